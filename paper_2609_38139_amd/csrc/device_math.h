@@ -79,109 +79,260 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
   return r;
 }
 
-// e^{-a} for a >= 0, by Cody-Waite reduction -a = k ln2 + r (ln2 split into
-// a head with 16 significant bits, so k*head is exact, and a tail), the
+// e^x for x <= 0, by Cody-Waite reduction x = k ln2 + r (ln2 split into a
+// head with 16 significant bits, so k*head is exact, and a tail), the
 // degree-7 Taylor polynomial of e^r in Horner form with one fused
-// multiply-add (v_fma_f32, a single rounding) per step, and a 2^k scale
-// built in the exponent field. Arguments above 80 (and +inf) give 0. The
-// evaluation has no branch: an argument above 80 is evaluated as 80 and the
-// result then replaced by 0, so every lane runs the same instructions and
-// the results for a <= 80 are those of the plain sequence.
-__device__ __forceinline__ float exp_neg(float a) {
-  const bool big = !(a <= 80.0f);
-  const float ln2_hi = __uint_as_float(0x3F317200u);
-  const float ln2_lo = (float)(0.69314718055994530942 - 0.693145751953125);
-  const float log2e = (float)1.44269504088896340736;
-  const float x = -(big ? 80.0f : a);
-  const float kf = floorf(fmaf(x, log2e, 0.5f));
-  const float r = fmaf(-kf, ln2_lo, fmaf(-kf, ln2_hi, x));
-  float p = 1.0f / 5040.0f;
-  p = fmaf(p, r, 1.0f / 720.0f);
-  p = fmaf(p, r, 1.0f / 120.0f);
-  p = fmaf(p, r, 1.0f / 24.0f);
-  p = fmaf(p, r, 1.0f / 6.0f);
-  p = fmaf(p, r, 0.5f);
-  p = fmaf(p, r, 1.0f);
-  p = fmaf(p, r, 1.0f);
-  const int k = (int)kf;
-  const float v = p * __uint_as_float((uint32_t)(k + 127) << 23);
-  return big ? 0.0f : v;
-}
-
+// multiply-add (a single rounding) per step, and a scale by 2^k: k, read off
+// the low bits of k + 1.5 2^23, is added to the exponent field (exact: for
+// x >= -80 the result is a normal number). Arguments below -80 (and -inf)
+// give 0: what the sequence makes of them is not used, so no lane diverges.
+//
 // log(1 + u) for u in [0, 1] as u Q(u), Q the degree-9 polynomial that
 // interpolates log(1 + u)/u at the 10 Chebyshev nodes of [0, 1] (computed in
 // high precision, coefficients rounded to FP32), in Horner form with one
 // fused multiply-add per step: no division, under 3 ulp of relative error.
-__device__ __forceinline__ float log1p_unit(float u) {
-  float q = -0x1.a04acap-9f;
-  q = fmaf(q, u, 0x1.402f4cp-6f);
-  q = fmaf(q, u, -0x1.cdd008p-5f);
-  q = fmaf(q, u, 0x1.afdde8p-4f);
-  q = fmaf(q, u, -0x1.38b908p-3f);
-  q = fmaf(q, u, 0x1.92b430p-3f);
-  q = fmaf(q, u, -0x1.ff0254p-3f);
-  q = fmaf(q, u, 0x1.554bd6p-2f);
-  q = fmaf(q, u, -0x1.ffffb8p-2f);
-  q = fmaf(q, u, 1.0f);
-  return u * q;
-}
+//
+// Both are chains of dependent multiply-adds: a wavefront alone issues such a
+// chain at one instruction in 10.7 clocks, two interleaved chains at one in
+// 7.3 and four at one in 5.8, and four wavefronts per SIMD issue 7% more with
+// four chains. The compiler schedules the chains one after another (it
+// minimises registers), so N chains are interleaved here in asm statements,
+// one instruction of each in turn. They read and write vector registers
+// only, and read one scalar constant.
+#define LAIM_X1(I) I(0)
+#define LAIM_X2(I) I(0) I(1)
+#define LAIM_X3(I) I(0) I(1) I(2)
+#define LAIM_X4(I) I(0) I(1) I(2) I(3)
 
-// log(1 + e^{-y}), y >= 0.
-__device__ __forceinline__ float softplus_neg(float y) { return log1p_unit(exp_neg(y)); }
+// Stage 1: t = floor(x log2e + 1/2), kb = t + 1.5 2^23, p = e^r's polynomial.
+#define LAIM_E0(i) "v_fma_f32 %[t" #i "], %[x" #i "], %[l], 0.5\n\t"
+#define LAIM_E1(i) "v_floor_f32 %[t" #i "], %[t" #i "]\n\t"
+#define LAIM_E2(i) "v_fmamk_f32 %[r" #i "], %[t" #i "], 0xbf317200, %[x" #i "]\n\t"  /* -ln2 head */
+#define LAIM_E3(i) "v_add_f32 %[k" #i "], 0x4b400000, %[t" #i "]\n\t"               /* + 1.5 2^23 */
+#define LAIM_E4(i) "v_fmamk_f32 %[r" #i "], %[t" #i "], 0xb5bfbe8e, %[r" #i "]\n\t"  /* -ln2 tail */
+#define LAIM_E5(i) "v_fmamk_f32 %[t" #i "], %[r" #i "], 0x39500d01, %[c]\n\t"        /* 1/5040, 1/720 */
+#define LAIM_E6(i) "v_fmaak_f32 %[t" #i "], %[t" #i "], %[r" #i "], 0x3c088889\n\t"  /* 1/120 */
+#define LAIM_E7(i) "v_fmaak_f32 %[t" #i "], %[t" #i "], %[r" #i "], 0x3d2aaaab\n\t"  /* 1/24 */
+#define LAIM_E8(i) "v_fmaak_f32 %[t" #i "], %[t" #i "], %[r" #i "], 0x3e2aaaab\n\t"  /* 1/6 */
+#define LAIM_E9(i) "v_fma_f32 %[t" #i "], %[t" #i "], %[r" #i "], 0.5\n\t"
+#define LAIM_EA(i) "v_fma_f32 %[t" #i "], %[t" #i "], %[r" #i "], 1.0\n\t"
+#define LAIM_EXP(X)                                                                             \
+  X(LAIM_E0) X(LAIM_E1) X(LAIM_E2) X(LAIM_E3) X(LAIM_E4) X(LAIM_E5) X(LAIM_E6) X(LAIM_E7)       \
+  X(LAIM_E8) X(LAIM_E9) X(LAIM_EA) X(LAIM_EA)
+// Stage 2: q = u Q(u).
+#define LAIM_L0(i) "v_fmamk_f32 %[q" #i "], %[u" #i "], 0xbb502565, %[c]\n\t"        /* -0x1.a04acap-9 */
+#define LAIM_L1(i) "v_fmaak_f32 %[q" #i "], %[q" #i "], %[u" #i "], 0xbd66e804\n\t"  /* -0x1.cdd008p-5 */
+#define LAIM_L2(i) "v_fmaak_f32 %[q" #i "], %[q" #i "], %[u" #i "], 0x3dd7eef4\n\t"  /* 0x1.afdde8p-4 */
+#define LAIM_L3(i) "v_fmaak_f32 %[q" #i "], %[q" #i "], %[u" #i "], 0xbe1c5c84\n\t"  /* -0x1.38b908p-3 */
+#define LAIM_L4(i) "v_fmaak_f32 %[q" #i "], %[q" #i "], %[u" #i "], 0x3e495a18\n\t"  /* 0x1.92b430p-3 */
+#define LAIM_L5(i) "v_fmaak_f32 %[q" #i "], %[q" #i "], %[u" #i "], 0xbe7f812a\n\t"  /* -0x1.ff0254p-3 */
+#define LAIM_L6(i) "v_fmaak_f32 %[q" #i "], %[q" #i "], %[u" #i "], 0x3eaaa5eb\n\t"  /* 0x1.554bd6p-2 */
+#define LAIM_L7(i) "v_fmaak_f32 %[q" #i "], %[q" #i "], %[u" #i "], 0xbeffffdc\n\t"  /* -0x1.ffffb8p-2 */
+#define LAIM_L8(i) "v_fma_f32 %[q" #i "], %[q" #i "], %[u" #i "], 1.0\n\t"
+#define LAIM_L9(i) "v_mul_f32 %[q" #i "], %[u" #i "], %[q" #i "]\n\t"
+#define LAIM_LOG(X)                                                                             \
+  X(LAIM_L0) X(LAIM_L1) X(LAIM_L2) X(LAIM_L3) X(LAIM_L4) X(LAIM_L5) X(LAIM_L6) X(LAIM_L7)       \
+  X(LAIM_L8) X(LAIM_L9)
+#define LAIM_EOUT(i) [t##i] "=&v"(t[i]), [r##i] "=&v"(r[i]), [k##i] "=&v"(kb[i])
+#define LAIM_EIN(i) [x##i] "v"(x[i])
+#define LAIM_LOUT(i) [q##i] "=&v"(o[i])
+#define LAIM_LIN(i) [u##i] "v"(u[i])
+
+// o[i] = log(1 + e^{x[i]}), x[i] <= 0, i < N <= 4.
+template <int N>
+__device__ __forceinline__ void softplus_nonpos(const float* x, float* o) {
+  static_assert(N >= 1 && N <= 4, "one to four chains");
+  const float log2e = (float)1.44269504088896340736;
+  const float c6 = 1.0f / 720.0f, q8 = 0x1.402f4cp-6f;
+  float t[N], r[N], kb[N], u[N];
+  if constexpr (N == 1)
+    asm(LAIM_EXP(LAIM_X1) : LAIM_EOUT(0) : LAIM_EIN(0), [l] "s"(log2e), [c] "v"(c6));
+  else if constexpr (N == 2)
+    asm(LAIM_EXP(LAIM_X2) : LAIM_EOUT(0), LAIM_EOUT(1) : LAIM_EIN(0), LAIM_EIN(1), [l] "s"(log2e), [c] "v"(c6));
+  else if constexpr (N == 3)
+    asm(LAIM_EXP(LAIM_X3)
+        : LAIM_EOUT(0), LAIM_EOUT(1), LAIM_EOUT(2)
+        : LAIM_EIN(0), LAIM_EIN(1), LAIM_EIN(2), [l] "s"(log2e), [c] "v"(c6));
+  else
+    asm(LAIM_EXP(LAIM_X4)
+        : LAIM_EOUT(0), LAIM_EOUT(1), LAIM_EOUT(2), LAIM_EOUT(3)
+        : LAIM_EIN(0), LAIM_EIN(1), LAIM_EIN(2), LAIM_EIN(3), [l] "s"(log2e), [c] "v"(c6));
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float v = __uint_as_float(__float_as_uint(t[i]) + (__float_as_uint(kb[i]) << 23));
+    u[i] = (x[i] < -80.0f) ? 0.0f : v;
+  }
+  if constexpr (N == 1)
+    asm(LAIM_LOG(LAIM_X1) : LAIM_LOUT(0) : LAIM_LIN(0), [c] "v"(q8));
+  else if constexpr (N == 2)
+    asm(LAIM_LOG(LAIM_X2) : LAIM_LOUT(0), LAIM_LOUT(1) : LAIM_LIN(0), LAIM_LIN(1), [c] "v"(q8));
+  else if constexpr (N == 3)
+    asm(LAIM_LOG(LAIM_X3)
+        : LAIM_LOUT(0), LAIM_LOUT(1), LAIM_LOUT(2)
+        : LAIM_LIN(0), LAIM_LIN(1), LAIM_LIN(2), [c] "v"(q8));
+  else
+    asm(LAIM_LOG(LAIM_X4)
+        : LAIM_LOUT(0), LAIM_LOUT(1), LAIM_LOUT(2), LAIM_LOUT(3)
+        : LAIM_LIN(0), LAIM_LIN(1), LAIM_LIN(2), LAIM_LIN(3), [c] "v"(q8));
+}
 
 // a [+] b = 2 atanh(tanh(a/2) tanh(b/2)) (the two-input sum-product check
 // rule; Hagenauer, Offer, Papke 1996), through its exact rewriting on the
 // magnitudes |a| [+] |b| = min + log(1 + e^{-(|a|+|b|)}) - log(1 + e^{-||a|-|b||}),
 // a negative rounding set to +0, and the sign sg(a) sg(b) with sg(x) = -1
-// iff x < 0 for a nonzero result (a zero result is +0).
-__device__ __forceinline__ float boxplus(float a, float b) {
-  const float aa = fabsf(a);
-  const float ab = fabsf(b);
-  const float mn = (ab < aa) ? ab : aa;
-  const float d = (aa < ab) ? (ab - aa) : (aa - ab);
-  float mag = (mn + softplus_neg(aa + ab)) - softplus_neg(d);
-  if (mag < 0.0f) mag = 0.0f;
-  const bool neg = (a < 0.0f) != (b < 0.0f);
-  return (neg && mag > 0.0f) ? -mag : mag;
+// iff x < 0 for a nonzero result (a zero result is +0). No input is -0 (sums
+// that start at +0 or a nonzero prior, and results of this function), so
+// sg() is the sign bit; adding +0 makes a zero result +0.
+// FAR: min(|a|, |b|) >= kBoxFar, where the first logarithm, at most 2.06e-7
+// (|a| + |b| >= 15.4), is under half an ulp of the minimum (2^-22 = 2.38e-7 in
+// [4, 8), more above): the sum rounds to the minimum and is not formed.
+// N pairs at once (N <= 4): o[i] = a[i] [+] b[i].
+constexpr float kBoxFar = 7.7f;
+template <bool FAR, int N>
+__device__ __forceinline__ void boxplus(const float* a, const float* b, float* o) {
+  float nd[N], ny[N], sd[N], sy[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    nd[i] = __uint_as_float(__float_as_uint(fabsf(a[i]) - fabsf(b[i])) | 0x80000000u);
+    ny[i] = -fabsf(a[i]) - fabsf(b[i]);
+  }
+  if constexpr (FAR) {
+    softplus_nonpos<N>(nd, sd);
+  } else {
+#pragma unroll
+    for (int i = 0; i + 1 < N; i += 2) {
+      const float x4[4] = {nd[i], ny[i], nd[i + 1], ny[i + 1]};
+      float o4[4];
+      softplus_nonpos<4>(x4, o4);
+      sd[i] = o4[0];
+      sy[i] = o4[1];
+      sd[i + 1] = o4[2];
+      sy[i + 1] = o4[3];
+    }
+    if constexpr (N & 1) {
+      const float x2[2] = {nd[N - 1], ny[N - 1]};
+      float o2[2];
+      softplus_nonpos<2>(x2, o2);
+      sd[N - 1] = o2[0];
+      sy[N - 1] = o2[1];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float mn = fminf(fabsf(a[i]), fabsf(b[i]));
+    const float mag = fmaxf((FAR ? mn : mn + sy[i]) - sd[i], 0.0f);
+    const uint32_t sg = __float_as_uint(a[i]) ^ __float_as_uint(b[i]);
+    o[i] = __uint_as_float((__float_as_uint(mag) & 0x7FFFFFFFu) | (sg & 0x80000000u)) + 0.0f;
+  }
+}
+__device__ __forceinline__ float boxplus1(float a, float b) {
+  float o;
+  boxplus<false, 1>(&a, &b, &o);
+  return o;
 }
 
 // The sum-product check rule's box-plus of all inputs but one, for every
 // output: acc[j] = F_{j-1} [+] B_{j+1} with the ascending prefix folds
 // F_k = F_{k-1} [+] x_k and the suffix folds B_k = x_k [+] B_{k+1}; an
 // empty side is dropped ((+inf) [+] y is y with -0 made +0, i.e. y + 0).
-// Inputs x[0 .. deg); deg = DC when REG. 3 (deg - 2) box-plus steps.
+// 3 (D - 2) box-plus steps in D - 2 stages of independent ones: stage S forms
+// F_S, B_{D-1-S} and the outputs whose two folds the stages before it made
+// (output j in stage max(j - 1, D - 2 - j) + 1: none, one or two a stage).
+template <int D, bool FAR, int S>
+__device__ __forceinline__ void boxplus_stage(const float* x, float* F, float* B, float* acc) {
+  if constexpr (S <= D - 2) {
+    constexpr int hi = S, lo = D - 1 - S;  // this stage's outputs, from the middle stage on
+    constexpr bool any = hi >= lo, both = hi > lo;
+    constexpr int N = both ? 4 : any ? 3 : 2;
+    float a[N], b[N], o[N];
+    a[0] = F[S - 1];
+    b[0] = x[S];
+    a[1] = x[D - 1 - S];
+    b[1] = B[D - S];
+    if constexpr (any) {
+      a[2] = F[hi - 1];
+      b[2] = B[hi + 1];
+    }
+    if constexpr (both) {
+      a[3] = F[lo - 1];
+      b[3] = B[lo + 1];
+    }
+    boxplus<FAR, N>(a, b, o);
+    F[S] = o[0];
+    B[D - 1 - S] = o[1];
+    if constexpr (any) acc[hi] = o[2];
+    if constexpr (both) acc[lo] = o[3];
+    boxplus_stage<D, FAR, S + 1>(x, F, B, acc);
+  }
+}
+template <int D, bool FAR>
+__device__ __forceinline__ void boxplus_folds(const float* x, float* acc) {
+  float F[D], B[D];
+  F[0] = x[0] + 0.0f;
+  B[D - 1] = x[D - 1] + 0.0f;
+  boxplus_stage<D, FAR, 1>(x, F, B, acc);
+  acc[0] = B[1];
+  acc[D - 1] = F[D - 2];
+}
+
+// The same, with FAR steps where they serve for every check that the
+// wavefront evaluates. A fold of i inputs is at least min - ln(i) (each step
+// takes off log(1 + e^{-d}) at most, ln 2 for two equal inputs), so inputs of
+// at least kBoxFar + ln(D - 1) + 0.01 make every step FAR (a step's roundings
+// are relative to its minimum, far below the 0.01). One compare and one
+// branch per check; half of the exponentials go in 38% of the
+// wavefront-checks of the 2D toric code L = 32 at p = 0.05, and in 71% of
+// those of the [[144,12,12]] code at p = 0.03.
+template <int D>
+__device__ __forceinline__ void boxplus_all(const float* x, float* acc) {
+  constexpr float kLn[] = {0.0f, 0.0f, 0.0f, 0.694f, 1.099f, 1.387f, 1.610f, 1.792f, 1.946f};
+  constexpr float bound = kBoxFar + kLn[D] + 0.01f;
+  float mn = fabsf(x[0]);
+#pragma unroll
+  for (int k = 1; k < D; ++k) mn = fminf(mn, fabsf(x[k]));
+  if (D > 2 && __builtin_amdgcn_ballot_w64(mn < bound) == 0ull)
+    boxplus_folds<D, true>(x, acc);
+  else
+    boxplus_folds<D, false>(x, acc);
+}
+
+// The folds of a check of degree deg in a variant with DC slots (REG: deg =
+// DC). Inputs x[0 .. deg). Wavefronts whose checks all have degree DC, or
+// all DC - 1, take the unrolled folds of that degree (the two degrees of the
+// spacetime window codes); mixed ones the folds with a condition per slot.
 template <int DC, bool REG>
 __device__ __forceinline__ void boxplus_others(const float* x, int32_t deg, float* acc) {
-  float F[DC], B[DC];
-  if (REG) {
-    F[0] = x[0] + 0.0f;
-#pragma unroll
-    for (int k = 1; k < DC - 1; ++k) F[k] = boxplus(F[k - 1], x[k]);
-    B[DC - 1] = x[DC - 1] + 0.0f;
-#pragma unroll
-    for (int k = DC - 2; k >= 1; --k) B[k] = boxplus(x[k], B[k + 1]);
-    acc[0] = B[1];
-    acc[DC - 1] = F[DC - 2];
-#pragma unroll
-    for (int j = 1; j < DC - 1; ++j) acc[j] = boxplus(F[j - 1], B[j + 1]);
-  } else {
-    F[0] = x[0] + 0.0f;
-#pragma unroll
-    for (int k = 1; k < DC; ++k) F[k] = (k < deg) ? boxplus(F[k - 1], x[k]) : F[k - 1];
-    B[DC - 1] = (DC - 1 < deg) ? x[DC - 1] + 0.0f : __builtin_inff();
-#pragma unroll
-    for (int k = DC - 2; k >= 0; --k)
-      B[k] = (k >= deg) ? __builtin_inff() : (k == deg - 1 ? x[k] + 0.0f : boxplus(x[k], B[k + 1]));
-#pragma unroll
-    for (int j = 0; j < DC; ++j) {
-      if (j >= deg) continue;
-      if (j == 0)
-        acc[j] = (deg >= 2) ? B[1] : __builtin_inff();
-      else if (j == deg - 1)
-        acc[j] = F[j - 1];
-      else
-        acc[j] = boxplus(F[j - 1], B[j + 1]);
+  if constexpr (REG) {
+    boxplus_all<DC>(x, acc);
+    return;
+  }
+  if constexpr (DC <= 6 && DC > 2) {
+    if (__builtin_amdgcn_ballot_w64(deg != DC) == 0ull) {
+      boxplus_all<DC>(x, acc);
+      return;
     }
+    if (__builtin_amdgcn_ballot_w64(deg != DC - 1) == 0ull) {
+      boxplus_all<DC - 1>(x, acc);
+      return;
+    }
+  }
+  float F[DC], B[DC];
+  F[0] = x[0] + 0.0f;
+#pragma unroll
+  for (int k = 1; k < DC; ++k) F[k] = (k < deg) ? boxplus1(F[k - 1], x[k]) : F[k - 1];
+  B[DC - 1] = (DC - 1 < deg) ? x[DC - 1] + 0.0f : __builtin_inff();
+#pragma unroll
+  for (int k = DC - 2; k >= 0; --k)
+    B[k] = (k >= deg) ? __builtin_inff() : (k == deg - 1 ? x[k] + 0.0f : boxplus1(x[k], B[k + 1]));
+#pragma unroll
+  for (int j = 0; j < DC; ++j) {
+    if (j >= deg) continue;
+    if (j == 0)
+      acc[j] = (deg >= 2) ? B[1] : __builtin_inff();
+    else if (j == deg - 1)
+      acc[j] = F[j - 1];
+    else
+      acc[j] = boxplus1(F[j - 1], B[j + 1]);
   }
 }
 

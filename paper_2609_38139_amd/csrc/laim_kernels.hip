@@ -322,7 +322,8 @@ constexpr int kMaxShotsPerBlock = 31;
 constexpr int kGroupWords = 16;  // per-group scratch words after msg
 // scratch word indices
 constexpr int kGwZero = 0, kGwLpar = 1 /* 4 words */, kGwFlips = 5, kGwDefects = 6, kGwInit = 7,
-              kGwAct0 = 8, kGwAct1 = 9, kGwChg0 = 10, kGwChg1 = 11, kGwLive = 12;
+              kGwAct0 = 8, kGwAct1 = 9, kGwChg0 = 10, kGwChg1 = 11, kGwLive = 12,
+              kGwFar = 13 /* a large message, read by padding checks */;
 constexpr int kFusedMaxWords = 4;  // logicals folded in LDS by the fused failure test
 
 template <bool B>
@@ -421,7 +422,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
   // ---- per-thread graph tables
   // A member owns checks t + k nt, k < CPT; those from m on pad the last
   // tile. Their LDS slots exist (mpad >= nt CPT) and they are swept like
-  // the others -- inputs from the zero word, syndrome 0 -- so that the
+  // the others -- inputs from a scratch word, syndrome 0 -- so that the
   // sweep needs no per-check condition; nothing reads what they write.
   // In the tiled variant slot j of a check's LDS messages is lattice
   // direction j, whose row slot is tile_jo; pidx of an input inside the tile
@@ -444,7 +445,9 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
         int32_t e = -1;
         if (valid && jr < c.dcmax && p < c.dvmax - 1)
           e = c.partner[((int64_t)ch * c.dcmax + jr) * (c.dvmax - 1) + p];
-        pidx[k][j][p] = (e >= 0) ? mword(edge_check(e), edge_slot(e)) : zslot;
+        // (a padding check reads a large message, so that it does not keep a
+        // wavefront from the short sum-product folds)
+        pidx[k][j][p] = (e >= 0) ? mword(edge_check(e), edge_slot(e)) : (valid ? zslot : zslot + kGwFar);
       }
     }
   }
@@ -474,6 +477,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
     if (t == 0) {
       gw[kGwZero] = (int32_t)0x80000000u;  // -0.0f
       for (int w = 1; w < kGroupWords; ++w) gw[w] = 0;
+      gw[kGwFar] = (int32_t)__float_as_uint(1000.0f);
     }
 #pragma unroll 1
     for (int32_t w = t; w < 3 * nw + ((c.m + 31) >> 5); w += u.nt) flw[w] = 0u;
