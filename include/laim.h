@@ -287,8 +287,10 @@ laim_status laim_decode_rounds_static(const laim_code* code, const laim_decode_p
                                       int32_t form, laim_stream stream);
 
 /* laim_resident_variant -- the resident kernel laim_decode_rounds (or, with
- * cfg, laim_decode_rounds_cfg) would run for these parameters: its template
- * degrees, checks per thread, and whether it is the tiled variant. The tiled
+ * cfg, laim_decode_rounds_cfg) would run for these parameters on a batch that
+ * fills the device (smaller batches take fewer checks per thread where the
+ * shape is left to the library): its template degrees, checks per thread, and
+ * whether it is the tiled variant. The tiled
  * variant runs min-sum on the 2D toric layout (checks i L + j, L a multiple
  * of 4, each sharing one qubit with each lattice neighbour) with 8 checks per
  * thread and m / 8 threads per shot: each thread's checks form a 2 x 4 tile,
@@ -302,14 +304,18 @@ laim_status laim_resident_variant(const laim_code* code, const laim_decode_param
                                   int32_t* checks_per_thread, int32_t* tiled);
 
 /* Sets the resident launch shape used from now on for this code and BP
- * rule (the autotuner's choice); cfg = NULL restores the built-in rule:
- * min-sum on the 2D toric layout takes the tiled variant (8 checks per
- * thread, m / 8 threads per shot, blocks near 128 threads with wavefronts at
- * least 80% full); otherwise 1, 2, 4 or 8 checks per thread for m up to 256,
- * 512, 1024 and beyond, and 256-thread blocks. A field given as 0 in cfg is
- * chosen by the same rule. */
+ * rule (the autotuner's choice); cfg = NULL restores the built-in rule. On a
+ * batch that fills the device: min-sum on the 2D toric layout takes the tiled
+ * variant (8 checks per thread, m / 8 threads per shot, blocks near 128 threads
+ * with wavefronts at least 80% full); other min-sum decodes take 1 to 8 checks
+ * per thread by the code's degrees, sum-product the fewest with at most 640
+ * threads per shot, in blocks of at most 256 threads (or one shot) with their
+ * wavefronts full. Smaller batches take the fewest checks per thread whose
+ * wavefronts the device holds at once. A field given as 0 in cfg is chosen by
+ * the same rule. */
 laim_status laim_set_resident_cfg(laim_code* code, int32_t bp, const laim_resident_cfg* cfg);
-/* The launch shape that would be used (after the built-in rule). */
+/* The launch shape that would be used for a batch that fills the device (after
+ * the built-in rule). */
 laim_status laim_get_resident_cfg(const laim_code* code, int32_t bp, laim_resident_cfg* cfg);
 
 /* laim_logical_failure -- decoder failure (Preliminaries): with r = e0 ^ z,

@@ -149,6 +149,13 @@ laim_status laim_batch_plan_create(const laim_batch_item* items, int32_t nitems,
     g->total += b.nshots;
     g->cost += (double)b.nshots * kp.rounds * std::max(kp.iters, 1) * b.code->E;
   }
+  // each group's launch shape is that of its shots in all
+  for (Group& gr : groups) {
+    const laim_resident_cfg* want = gr.code->has_cfg[gr.kp.bp] ? &gr.code->cfg[gr.kp.bp] : nullptr;
+    if (!resident_shape(gr.code->dev, gr.kp.bp, want, &gr.sh, device, gr.kp.conflict == kConflictSequential,
+                        reg_dv2_ok(gr.kp), gr.total))
+      return LAIM_EUNSUP;  // (not reached: the same code fitted above)
+  }
   // the largest groups first
   std::stable_sort(groups.begin(), groups.end(), [](const Group& a, const Group& b) { return a.cost > b.cost; });
   laim_batch_plan* plan = new (std::nothrow) laim_batch_plan();

@@ -1246,7 +1246,14 @@ struct ResJobs {
   uint32_t* counter;
   int32_t spb;
   // Takes the next spb shots from the launch's queue; false once it is empty.
+  // A launch with a block for every group of spb shots has no queue (counter
+  // null): block b takes shots b spb .. and ends.
   __device__ bool next(int32_t* ctrl) {
+    if (!counter) {
+      if (base >= 0) return false;
+      base = (int32_t)bid_x() * spb;
+      return true;
+    }
     __syncthreads();
     if (tid_x() == 0) ctrl[0] = (int32_t)atomicAdd(counter, (uint32_t)spb);
     __syncthreads();
@@ -1294,7 +1301,7 @@ __device__ __forceinline__ void resident_body(const DevCode& c, const KParams& k
   // control words after the groups, so that group 0's messages start at
   // LDS address 0 and the slot offsets fit the LDS instructions' offset fields
   int32_t* ctrl = reinterpret_cast<int32_t*>(smem + (size_t)a.u.spb * a.u.group_bytes);
-  ResJobs jobs{a.items, a.nitems, a.e0,     a.s0,     a.r0,      a.shot0,   a.nshots, c.n, c.m, 0,
+  ResJobs jobs{a.items, a.nitems, a.e0,     a.s0,     a.r0,      a.shot0,   a.nshots, c.n, c.m, -1,
                a.z,     a.s,      a.tclr,   a.L,      a.fail,    a.sweeps,  a.counter, a.u.spb};
   run_units<DC, DV, CPT, BP, REG, ResJobs, TILE>(c, kp, a.u, jobs, smem, ctrl);
 }
@@ -1465,8 +1472,81 @@ static size_t group_bytes_for(int dc, int mpad, int n, int m, bool seq) {
   return (b + 15) / 16 * 16;
 }
 
+// Compute units of a device (256 if it cannot be asked).
+static int device_cus(int device) {
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) cus = 256;
+  return cus;
+}
+
+// Checks per thread by the built-in rule, for nshots shots (0: a batch that
+// fills the device). Fewer checks per thread make a sweep of one shot shorter
+// (a wavefront alone issues one instruction in about 5 clocks, so a thread's
+// checks run one after another); more of them amortise the barriers, the
+// round's bookkeeping and, in the tiled variant, keep messages in registers,
+// which pays once the device is full.
+//  - Full device, min-sum: 8 for (4, 2) and the tiled variant, 4 for (6, 2) and
+//    (2, 2), 2 for (4, 4), 1 for (6, 3) and the padded variants' 2 -- measured
+//    in ms at 1 / 2 / 4 / 8 checks per thread: 2D toric L = 21, 16,384 shots
+//    1.76 / 0.95 / 0.81 / 0.77; 3D point L = 12, 8,192 shots - / 29.4 / 20.1 /
+//    27.2 (8 spills); membrane L = 8, 8,192 shots - / 1.73 / 1.91; [[144,12,12]],
+//    131,072 shots 2.2 / 2.4 / 3.7; repetition d = 101, 131,072 shots 1.05 /
+//    0.66 / 0.56 / 0.57. At least kMinThreads threads per shot, since below
+//    that a wavefront holds many shots that wait for the slowest.
+//  - Full device, sum-product: the fewest with at most 640 threads per shot (2D
+//    toric L = 32, 16,384 shots 26.9 / 23.3 / 25.7 / 30.9; 3D point L = 12, 4,096
+//    shots - / 37.4 / 33.3 / 39.6); checks of degree 2 have no box-plus step
+//    and follow the min-sum rule.
+//  - Otherwise the fewest whose wavefronts number at most kFewWaves per SIMD
+//    (2D toric L = 16, min-sum, 1,024 shots, 4 per SIMD at one check per thread:
+//    0.112 ms against 0.182 with the tiled variant; 4,096 shots 0.232 against
+//    0.231).
+static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool tile_ok, int64_t nshots, int cus) {
+  constexpr int kMaxBlock = 1024, kMinThreads = 40, kFewWaves = 4;
+  auto threads = [&](int cpt) { return (c.m + cpt - 1) / cpt; };
+  auto usable = [&](int cpt) { return threads(cpt) <= kMaxBlock && find_variant(dc, dv, cpt, bp, reg); };
+  static const int order[] = {1, 2, 4, 8};
+  int full = 0;
+  if (bp != 0 && dc > 2) {
+    for (int a : order)
+      if (!full && usable(a) && threads(a) <= 640) full = a;
+  } else if (tile_ok) {
+    full = 8;
+  } else {
+    const int most = !reg ? 4 : dc == 2 ? 4 : dv == 3 ? 1 : dv == 4 ? 2 : dc == 6 ? 4 : 8;
+    const int least = dc == 2 ? 24 : kMinThreads;
+    for (int a : order)
+      if (usable(a) && (!full || (a <= most && threads(a) >= least))) full = a;
+  }
+  for (int i = 3; i >= 0 && !full; --i)  // no shape within 1024 threads: the largest (rejected by the caller)
+    if (find_variant(dc, dv, order[i], bp, reg)) full = order[i];
+  if (nshots > 0)
+    for (int a : order)
+      if (a < full && usable(a) && nshots * ((threads(a) + 63) / 64) <= (int64_t)kFewWaves * 4 * cus) return a;
+  return full;
+}
+
+// Shots per block by the built-in rule: fills the wavefronts of a block of
+// at most 256 threads, the fewest shots first (each further one has to add 2%
+// of lanes in use: the shots of a block run in lockstep and wait for the
+// slowest). [[144,12,12]] (72 threads) takes 3, [[72,12,6]] (36) 7, 125 threads
+// one (3D point L = 5, min-sum, 16,384 shots: 0.56 ms as 63 x 2 x 1 against 0.81
+// as 125 x 1 x 2).
+static int built_in_spb(int nt) {
+  int best = 1;
+  double most = -1.0;
+  for (int s = 1; s <= kMaxShotsPerBlock && (s == 1 || nt * s <= 256); ++s) {
+    const double use = (double)(nt * s) / (64.0 * ((nt * s + 63) / 64)) - 0.02 * s;
+    if (use > most + 1e-9) {
+      most = use;
+      best = s;
+    }
+  }
+  return best;
+}
+
 bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, ResidentShape* out,
-                    int device, bool seq, bool reg2) {
+                    int device, bool seq, bool reg2, int64_t nshots) {
   int dc, dv, reg;
   if (!pick_degrees(c, reg2, &dc, &dv, &reg)) {
     set_error("resident form needs check degree <= 8 and qubit degree <= 4 (have %d, %d)", c.dcmax,
@@ -1481,15 +1561,12 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
   int cpt = want ? want->checks_per_thread : 0;
   int nt = want ? want->threads_per_shot : 0;
   int spb = want ? want->shots_per_block : 0;
-  // min-sum on the 2D toric layout: the tiled variant, faster than the
-  // other shapes at every L measured (8 to 64)
+  // min-sum on the 2D toric layout: the tiled variant, on a full device faster
+  // than the other shapes at every L measured (8 to 64)
   const bool tile_ok = c.tile_chk && bp == 0 && dc == 4 && dv == 2 && reg && !seq;
-  if (cpt <= 0 && nt <= 0 && tile_ok) cpt = 8;
+  if (cpt <= 0 && nt <= 0) cpt = built_in_cpt(c, bp, dc, dv, reg, tile_ok, nshots, device_cus(device));
   if (cpt <= 0) {
-    if (nt > 0)
-      cpt = (c.m + nt - 1) / nt;
-    else
-      cpt = (c.m <= 256) ? 1 : (c.m <= 512 ? 2 : (c.m <= 1024 ? 4 : 8));
+    cpt = (c.m + nt - 1) / nt;
     int allowed[] = {1, 2, 4, 8};
     int pick = -1;
     for (int a : allowed)
@@ -1530,7 +1607,12 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
     }
     spb = best > 0 ? best : 1;
   }
-  if (spb <= 0) spb = (nt >= 256) ? 1 : 256 / nt;
+  if (spb <= 0) {
+    spb = built_in_spb(nt);
+    // as many as the LDS holds (and not more than there are)
+    const size_t gb1 = group_bytes_for(dc, (nt * cpt + 63) / 64 * 64, c.n, c.m, seq);
+    while (spb > 1 && (kCtrlWords * 4 + gb1 * (size_t)spb > (size_t)lds_max || (nshots > 0 && spb > nshots))) --spb;
+  }
   if (spb > kMaxShotsPerBlock) spb = kMaxShotsPerBlock;
   if (nt * spb > 1024) {
     set_error("block of %d threads exceeds 1024", nt * spb);
@@ -1638,8 +1720,9 @@ hipError_t launch_sweep_count(const KParams& kp, const int32_t* tclr, int32_t ns
 size_t resident_workspace_bytes() { return 256; }
 
 // The persistent launch of a resident kernel variant: as many blocks as fit
-// on the device at once (at most one per group of shots); the shot queue
-// in a.counter is cleared first by a kernel (no memset node in a graph).
+// on the device at once (at most one per group of shots). Where groups are
+// left over, blocks take them from the queue in a.counter, cleared first by a
+// kernel (no memset node in a graph).
 static hipError_t launch_resident_args(const DevCode& c, const KParams& kp, const ResidentShape& sh,
                                        ResArgs& a, int32_t total, hipStream_t st) {
   if (sh.reg && sh.dv == 2 && !reg_dv2_ok(kp)) return hipErrorInvalidValue;
@@ -1653,26 +1736,31 @@ static hipError_t launch_resident_args(const DevCode& c, const KParams& kp, cons
   a.u.rounds = kp.rounds;
   a.u.resume = 0;
   a.u.events = 0;
-  hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, st, a.counter, 1);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
   if (sh.lds > 64 * 1024) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(var->fn),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds);
     (void)hipGetLastError();
   }
-  int per_cu = 0;
-  err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(var->fn),
-                                                     sh.nt * sh.spb, sh.lds);
-  if (err != hipSuccess) return err;
-  if (per_cu < 1) return hipErrorInvalidConfiguration;
-  int dev = 0, cus = 0;
+  int dev = 0;
   (void)hipGetDevice(&dev);
-  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (cus <= 0) cus = 256;
+  const int64_t cus = device_cus(dev);
   const int64_t groups = ((int64_t)total + sh.spb - 1) / sh.spb;
-  int64_t blocks = (int64_t)per_cu * cus;
-  if (blocks > groups) blocks = groups;
+  int64_t blocks = groups;
+  if (groups > cus) {  // (up to one block per CU run at once whatever the occupancy)
+    int per_cu = 0;
+    const hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &per_cu, reinterpret_cast<const void*>(var->fn), sh.nt * sh.spb, sh.lds);
+    if (err != hipSuccess) return err;
+    if (per_cu < 1) return hipErrorInvalidConfiguration;
+    if (blocks > per_cu * cus) blocks = per_cu * cus;
+  }
+  if (blocks == groups) {
+    a.counter = nullptr;  // one unit per block: no queue to clear, one launch less (4 us of a short call)
+  } else {
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, st, a.counter, 1);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
   hipLaunchKernelGGL(var->fn, dim3((unsigned)blocks), dim3(sh.nt * sh.spb), sh.lds, st, c, kp, a);
   return hipGetLastError();
 }

@@ -1,0 +1,54 @@
+"""The built-in launch shape over the batch sizes where it changes.
+
+The rule takes fewer checks per thread for a batch too small to fill the
+device (one block per shot group and no shot queue while every group has a
+block of its own), and the shape never changes a result: each batch is
+compared bit for bit with the same shots under an explicit shape, and the
+smallest with the oracle.
+"""
+import numpy as np
+import pytest
+
+from paper_2609_38139_amd import codes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def L():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("a GPU test ran without a visible GPU")
+    from paper_2609_38139_amd import laim
+    laim.lib()
+    return laim
+
+
+# (code, an explicit shape to compare with)
+CASES = [("toric2d:8", (8, 8)), ("toric2d:13", (169, 1)), ("toric2d:21", (221, 2)), ("bb:6x6", (36, 1)),
+         ("bb:12x6", (36, 2)), ("toric3d_point:5", (63, 2)), ("toric3d_membrane:4", (192, 1)), ("rep:101", (51, 2)),
+         ("rep:9", (9, 1))]
+
+
+@pytest.mark.parametrize("conflict", ["or", "sequential"])
+@pytest.mark.parametrize("bp", ["minsum", "sumproduct"])
+@pytest.mark.parametrize("name,shape", CASES)
+def test_results_do_not_depend_on_the_batch_size(L, orc, name, shape, bp, conflict):
+    import torch
+    spec = codes.by_name(name)
+    dc = L.Code(spec, 0)
+    q = 0.125 if "membrane" in name else 0.05
+    P = L.DecodeParams(bp=bp, q=q, rounds=8, conflict=conflict, seed=5)
+    cfg = {"threads_per_shot": shape[0], "checks_per_thread": shape[1], "shots_per_block": 1}
+    e0 = L.sample_noise(dc, 0.05, 3, 0, 4500)
+    ref = L.decode_rounds(dc, P, e0, cfg=cfg, want_beliefs=True, want_fail=True)
+    o = orc.decode(spec, orc.DecodeParams(bp=bp, q=q, rounds=8, conflict=conflict, seed=5), e0[:40].cpu().numpy(),
+                   want_beliefs=True)
+    for k in ("z", "s", "tclr"):
+        assert np.array_equal(ref[k][:40].cpu().numpy(), o[k]), k
+    for S in (1, 2, 7, 255, 256, 257, 1024, 1500, 4500):
+        print(f"[shape] {name} {bp} {conflict} shots={S}", flush=True)
+        g = L.decode_rounds(dc, P, e0[:S].contiguous(), want_beliefs=True, want_fail=True)
+        for k in ("z", "s", "tclr", "fail"):
+            assert torch.equal(g[k], ref[k][:S]), (S, k)
+        assert torch.equal(g["L"].view(torch.int32), ref["L"][:S].view(torch.int32)), S
