@@ -202,7 +202,10 @@ typedef struct {
 
 /* Execution forms of laim_decode_rounds; all give identical results. */
 #define LAIM_FORM_AUTO 0     /* resident if the code fits in LDS (and, for min-sum,
-                                alpha <= 1), else stream */
+                                alpha <= 1), else stream; larger regular codes of the
+                                compiled degrees run one block per shot with their
+                                messages in LDS and device memory (the workspace and
+                                sweeps_out are the stream form's) */
 #define LAIM_FORM_RESIDENT 1 /* one persistent launch, per-shot state in LDS/registers */
 #define LAIM_FORM_STREAM 2   /* messages in HBM, one launch per BP sweep and per phase */
 
@@ -508,8 +511,8 @@ laim_status laim_decode_online(const laim_online_plan* plan, const laim_decode_p
  * graph that laim_batch_plan_launch replays. Inputs and outputs are read and
  * written at the addresses given at creation. Items whose code cannot run in
  * the resident form (a shot's state larger than the LDS, degrees beyond the
- * compiled variants, or min-sum with alpha > 1) run in the stream form,
- * recorded in the same graph after the persistent launch; the plan owns
+ * compiled variants, or min-sum with alpha > 1) run as LAIM_FORM_AUTO runs
+ * them, recorded in the same graph after the persistent launch; the plan owns
  * their HBM workspace. Results never depend on which form an item takes.
  */
 typedef struct {

@@ -203,8 +203,13 @@ laim_status laim_batch_plan_create(const laim_batch_item* items, int32_t nitems,
   for (size_t k = 0; k < stream_items.size() && e == hipSuccess; ++k) {
     const laim_batch_item& b = items[stream_items[k].index];
     if (b.nshots == 0) continue;
-    e = launch_stream(b.code->dev, stream_items[k].kp, b.e0, b.shot0, b.nshots, base + stream_off[k], b.z_out,
-                      b.s_out, b.tclr_out, nullptr, plan->cap);
+    const KParams& kp = stream_items[k].kp;
+    e = wide_ok(b.code->dev, kp)
+            ? launch_wide(b.code->dev, kp, b.e0, b.shot0, b.nshots, base + stream_off[k],
+                          stream_workspace_bytes(b.code->dev, b.nshots, false), b.z_out, b.s_out, b.tclr_out, nullptr,
+                          plan->cap)
+            : launch_stream(b.code->dev, kp, b.e0, b.shot0, b.nshots, base + stream_off[k], b.z_out, b.s_out,
+                            b.tclr_out, nullptr, plan->cap);
     if (e == hipSuccess && b.fail_out)
       e = launch_failure(b.code->dev, b.e0, b.z_out, b.nshots, b.fail_out, plan->cap);
   }

@@ -144,6 +144,15 @@ hipError_t launch_stream(const DevCode& c, const KParams& kp, const uint8_t* e0,
                          int32_t nshots, void* ws, uint8_t* z, uint8_t* s, int32_t* tclr, float* L,
                          hipStream_t st, const uint8_t* s0 = nullptr, int32_t r0 = 0);
 
+// ---- the wide form (laim_wide.hip): regular codes of more than
+// kWideMinChecks checks that cannot run resident, under AUTO only
+constexpr int32_t kWideMinChecks = 4096;
+bool wide_ok(const DevCode& c, const KParams& kp);
+// ws: at least stream_workspace_bytes for the same shots
+hipError_t launch_wide(const DevCode& c, const KParams& kp, const uint8_t* e0, uint64_t shot0, int32_t nshots,
+                       void* ws, size_t ws_bytes, uint8_t* z, uint8_t* s, int32_t* tclr, float* L, hipStream_t st,
+                       const uint8_t* s0 = nullptr, int32_t r0 = 0);
+
 // ---- multi-code kernels (batched plans and the serving loop)
 // Block-uniform description of a unit: the launch shape of one code, the
 // rounds to run, and whether groups resume from saved state.
