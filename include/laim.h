@@ -561,7 +561,8 @@ typedef struct {
 
 /* Creates a server on `device` with a device-memory budget for request
  * state (per request about n + 4 m d_c + n + m + 256 bytes, 256-aligned
- * parts) and at most max_slots requests advanced per step. Requests must
+ * parts) and at most max_slots requests advanced per step; the step's tables
+ * and at most 16 MiB of results take pinned host memory. Requests must
  * use codes with check degree <= 8 and qubit degree <= 4 (min-sum with
  * alpha <= 1). */
 laim_status laim_server_create(int32_t device, size_t mem_budget_bytes, int32_t max_slots,

@@ -37,7 +37,7 @@ int cu_count(int device) {
 // Resolves one code + parameters into the device record of the multi-code
 // kernels (shape, variant) and its LDS/block needs.
 laim_status make_item(const laim_code* code, const laim_decode_params* params, BatchItemDev* it,
-                      size_t* lds, int* block) {
+                      bool few, size_t* lds, int* block) {
   KParams kp;
   laim_status st = resolve_params(params, &kp);
   if (st != LAIM_OK) return st;
@@ -50,7 +50,7 @@ laim_status make_item(const laim_code* code, const laim_decode_params* params, B
   it->kp = kp;
   const laim_resident_cfg* want = code->has_cfg[kp.bp] ? &code->cfg[kp.bp] : nullptr;
   if (!batch_variant(code->dev, kp.bp, want, code->device, kp.conflict == kConflictSequential,
-                     reg_dv2_ok(kp), &it->u, &it->variant, lds, block))
+                     reg_dv2_ok(kp), few, &it->u, &it->variant, lds, block))
     return LAIM_EUNSUP;
   it->u.rounds = kp.rounds;
   return LAIM_OK;
@@ -314,6 +314,8 @@ struct Request {
   bool resident = false, done = false;
   size_t off = 0, bytes = 0;  // arena block
   size_t o_e0, o_msg, o_z, o_s, o_hdr;
+  bool has_res = false;  // z and s arrive in host memory (offset res_off of the result slab)
+  size_t res_off = 0;
   int32_t tclr = -1, fail = 0;
   int64_t t_ready = 0;
 };
@@ -343,13 +345,19 @@ int64_t now_ns() {
 
 }  // namespace
 
+// Pinned memory for the results of finished requests, per server (at most its
+// device budget): about 2,000 requests of 2D toric L = 48.
+constexpr size_t kResultSlabBytes = 16u << 20;
+
 struct laim_server {
   int device = 0;
   int max_slots = 0;
   hipStream_t st = nullptr;
   void* arena_mem = nullptr;
   Arena arena;
-  // item table (one record per distinct code + parameters), on host and device
+  // item table (two records per distinct code + parameters -- 2 i with the
+  // launch shape of a full device, 2 i + 1 with that of few requests), on host
+  // and device
   std::vector<BatchItemDev> items;
   std::vector<std::vector<char>> item_keys;
   std::vector<size_t> item_lds;
@@ -357,13 +365,17 @@ struct laim_server {
   BatchItemDev* items_dev = nullptr;
   size_t items_dev_cap = 0;
   bool items_dirty = false;
-  // per-step tables (pinned host, device)
+  // per-step tables in pinned host memory, which the kernel reads (requests,
+  // units) and writes (events) directly
   ServerReqDev* reqs_h = nullptr;
   ServerUnitDev* units_h = nullptr;
   int32_t* ev_h = nullptr;
-  ServerReqDev* reqs_d = nullptr;
-  ServerUnitDev* units_d = nullptr;
-  int32_t* ev_d = nullptr;
+  ServerReqDev* reqs_d = nullptr;  // each block's copy of its requests
+  // z and s of finished requests, written by the kernel (pinned host memory;
+  // requests that find no room are read back from the arena)
+  uint8_t* res_h = nullptr;
+  Arena res;
+  int cus = 256;
   std::map<uint64_t, Request> reqs;
   std::deque<uint64_t> waiting;
   uint64_t next_ticket = 1;
@@ -392,14 +404,16 @@ laim_status laim_server_create(int32_t device, size_t mem_budget_bytes, int32_t 
   if (e == hipSuccess) e = hipHostMalloc((void**)&s->units_h, sizeof(ServerUnitDev) * max_slots, 0);
   if (e == hipSuccess) e = hipHostMalloc((void**)&s->ev_h, sizeof(int32_t) * 4 * max_slots, 0);
   if (e == hipSuccess) e = hipMalloc((void**)&s->reqs_d, sizeof(ServerReqDev) * max_slots);
-  if (e == hipSuccess) e = hipMalloc((void**)&s->units_d, sizeof(ServerUnitDev) * max_slots);
-  if (e == hipSuccess) e = hipMalloc((void**)&s->ev_d, sizeof(int32_t) * 4 * max_slots);
+  const size_t slab = std::min<size_t>(mem_budget_bytes, kResultSlabBytes) / 256 * 256;
+  if (e == hipSuccess) e = hipHostMalloc((void**)&s->res_h, slab, 0);
   if (e != hipSuccess) {
     laim_status st = hip_fail(e, "creating the server");
     laim_server_destroy(s);
     return st == LAIM_EHIP ? LAIM_ENOMEM : st;
   }
   s->arena.init(mem_budget_bytes);
+  s->res.init(slab);
+  s->cus = device_cus(device);
   *out = s;
   return LAIM_OK;
 }
@@ -412,8 +426,7 @@ void laim_server_destroy(laim_server* s) {
   if (s->units_h) (void)hipHostFree(s->units_h);
   if (s->ev_h) (void)hipHostFree(s->ev_h);
   if (s->reqs_d) (void)hipFree(s->reqs_d);
-  if (s->units_d) (void)hipFree(s->units_d);
-  if (s->ev_d) (void)hipFree(s->ev_d);
+  if (s->res_h) (void)hipHostFree(s->res_h);
   if (s->items_dev) (void)hipFree(s->items_dev);
   if (s->arena_mem) (void)hipFree(s->arena_mem);
   if (s->st) (void)hipStreamDestroy(s->st);
@@ -468,23 +481,27 @@ laim_status laim_server_submit(laim_server* s, const laim_code* code,
   for (size_t i = 0; i < s->item_keys.size(); ++i)
     if (s->item_keys[i] == key) item = (int)i;
   if (item < 0) {
-    BatchItemDev it;
-    size_t lds = 0;
-    int block = 0;
-    laim_status st = make_item(code, params, &it, &lds, &block);
-    if (st != LAIM_OK) return st;
-    item = (int)s->items.size();
-    s->items.push_back(it);
+    BatchItemDev it[2];
+    size_t lds[2] = {0, 0};
+    int block[2] = {0, 0};
+    for (int f = 0; f < 2; ++f) {
+      laim_status st = make_item(code, params, &it[f], f == 1, &lds[f], &block[f]);
+      if (st != LAIM_OK) return st;
+    }
+    item = (int)s->item_keys.size();
     s->item_keys.push_back(key);
-    s->item_lds.push_back(lds);
-    s->item_block.push_back(block);
+    for (int f = 0; f < 2; ++f) {
+      s->items.push_back(it[f]);
+      s->item_lds.push_back(lds[f]);
+      s->item_block.push_back(block[f]);
+    }
     s->items_dirty = true;
   }
   Request r;
   r.ticket = s->next_ticket++;
   r.code = code;
   r.item = item;
-  r.bp = s->items[item].kp.bp;
+  r.bp = s->items[2 * item].kp.bp;
   r.shot = shot_id;
   r.rounds_total = params->rounds;
   r.retire = params->retire ? 1 : 0;
@@ -537,6 +554,7 @@ laim_status laim_server_step(laim_server* s, laim_server_event* events, int32_t 
       s->arena.release(r.off, r.bytes);
       return hip_fail(e, "admitting a request");
     }
+    r.has_res = s->res.alloc((size_t)c->n + c->m, &r.res_off);
     r.resident = true;
     s->waiting.pop_front();
     ++resident;
@@ -573,6 +591,11 @@ laim_status laim_server_step(laim_server* s, laim_server_event* events, int32_t 
     const int ky = y.bp * 1000000 + y.item * 3 + phase(y);
     return kx < ky;
   });
+  // Requests too few to fill the device take the shape with the fewest checks
+  // per thread (at most 4 wavefronts per SIMD in all, as the decode calls).
+  int64_t waves = 0;
+  for (uint64_t t : order) waves += (s->items[2 * s->reqs.at(t).item + 1].u.nt + 63) / 64;
+  const int few = waves <= (int64_t)16 * s->cus ? 1 : 0;
   int nreq = 0, nunit = 0;
   int unit_first[2] = {-1, -1}, unit_count[2] = {0, 0};
   size_t lds[2] = {0, 0};
@@ -583,41 +606,38 @@ laim_status laim_server_step(laim_server* s, laim_server_event* events, int32_t 
     ServerReqDev q;
     q.shot = r.shot;
     q.round = r.round;
-    q.pad = 0;
+    q.last = r.round + 1 >= r.rounds_total ? 1 : 0;
     q.e0 = (const uint8_t*)(A + r.o_e0);
     q.msg = (float*)(A + r.o_msg);
     q.z = (uint8_t*)(A + r.o_z);
     q.s = (uint8_t*)(A + r.o_s);
     q.hdr = (int32_t*)(A + r.o_hdr);
     q.fail = (uint8_t*)(A + r.o_hdr + 16);
-    q.ev = s->ev_d + 4 * nreq;
+    q.ev = s->ev_h + 4 * nreq;
+    q.res = r.has_res ? s->res_h + r.res_off : nullptr;
     s->reqs_h[nreq] = q;
-    const BatchItemDev& it = s->items[r.item];
+    const int rec = 2 * r.item + few;
+    const BatchItemDev& it = s->items[rec];
     const bool resume = r.round > 0;
     const int32_t nround = r.rounds_total > 0 ? 1 : 0;
-    const bool new_unit = nunit == 0 || s->units_h[nunit - 1].item != r.item ||
+    const bool new_unit = nunit == 0 || s->units_h[nunit - 1].item != rec ||
                           s->units_h[nunit - 1].resume != (resume ? 1 : 0) ||
                           s->units_h[nunit - 1].rounds != nround ||
                           s->units_h[nunit - 1].count >= it.u.spb;
     if (new_unit) {
       if (unit_first[r.bp] < 0) unit_first[r.bp] = nunit;
       ++unit_count[r.bp];
-      s->units_h[nunit++] = ServerUnitDev{r.item, nreq, 0, resume ? 1 : 0, nround};
-      lds[r.bp] = std::max(lds[r.bp], s->item_lds[r.item]);
-      block[r.bp] = std::max(block[r.bp], s->item_block[r.item]);
+      s->units_h[nunit++] = ServerUnitDev{rec, nreq, 0, resume ? 1 : 0, nround};
+      lds[r.bp] = std::max(lds[r.bp], s->item_lds[rec]);
+      block[r.bp] = std::max(block[r.bp], s->item_block[rec]);
     }
     s->units_h[nunit - 1].count++;
     ++nreq;
   }
-  e = hipMemcpyAsync(s->reqs_d, s->reqs_h, sizeof(ServerReqDev) * nreq, hipMemcpyHostToDevice, s->st);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(s->units_d, s->units_h, sizeof(ServerUnitDev) * nunit, hipMemcpyHostToDevice, s->st);
   for (int bp = 0; bp < 2 && e == hipSuccess; ++bp)
     if (unit_count[bp])
-      e = launch_server(bp, s->items_dev, s->units_d + unit_first[bp], unit_count[bp], s->reqs_d,
+      e = launch_server(bp, s->items_dev, s->units_h + unit_first[bp], unit_count[bp], s->reqs_h, s->reqs_d,
                         lds[bp], block[bp], s->st);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(s->ev_h, s->ev_d, sizeof(int32_t) * 4 * nreq, hipMemcpyDeviceToHost, s->st);
   if (e == hipSuccess) e = hipStreamSynchronize(s->st);
   if (e != hipSuccess) return hip_fail(e, "server step");
   const int64_t t = now_ns();
@@ -664,12 +684,19 @@ laim_status laim_server_result(laim_server* s, uint64_t ticket, uint8_t* z_host,
     set_error("request %llu is not finished", (unsigned long long)ticket);
     return LAIM_EBUSY;
   }
-  DeviceGuard g(s->device);
-  hipError_t e = hipSuccess;
-  char* A = (char*)s->arena_mem;
-  if (z_host) e = hipMemcpy(z_host, A + r.o_z, r.code->n, hipMemcpyDeviceToHost);
-  if (e == hipSuccess && s_host) e = hipMemcpy(s_host, A + r.o_s, r.code->m, hipMemcpyDeviceToHost);
-  if (e != hipSuccess) return hip_fail(e, "reading a result");
+  if (r.has_res) {  // written by the kernel of the request's last round
+    const uint8_t* p = s->res_h + r.res_off;
+    if (z_host) memcpy(z_host, p, r.code->n);
+    if (s_host) memcpy(s_host, p + r.code->n, r.code->m);
+    s->res.release(r.res_off, (size_t)r.code->n + r.code->m);
+  } else {
+    DeviceGuard g(s->device);
+    hipError_t e = hipSuccess;
+    char* A = (char*)s->arena_mem;
+    if (z_host) e = hipMemcpy(z_host, A + r.o_z, r.code->n, hipMemcpyDeviceToHost);
+    if (e == hipSuccess && s_host) e = hipMemcpy(s_host, A + r.o_s, r.code->m, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(e, "reading a result");
+  }
   if (tclr) *tclr = r.tclr;
   s->arena.release(r.off, r.bytes);
   s->reqs.erase(it);

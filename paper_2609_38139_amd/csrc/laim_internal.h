@@ -201,18 +201,21 @@ struct ServerUnitDev {
 struct ServerReqDev {
   uint64_t shot;
   int32_t round;  // rounds already run
-  int32_t pad;
+  int32_t last;   // 1: this is the last round of the request's budget
   const uint8_t* e0;  // [n]
   float* msg;         // [m * dcmax]
   uint8_t* z;         // [n]
   uint8_t* s;         // [m]
   int32_t* hdr;       // [4]: t_clr, messages at a fixed point (0/1)
-  int32_t* ev;        // [2]: flips, syndrome weight
+  int32_t* ev;        // [4] in host memory: flips, syndrome weight, t_clr, failure and frozen bits
   uint8_t* fail;      // [1]
+  uint8_t* res;       // [n + m] in host memory or null: z and s of a request that finishes
 };
 
+// few: the shape for requests too few to fill the device (the fewest checks
+// per thread), else that of a full one
 bool batch_variant(const DevCode& c, int bp, const laim_resident_cfg* want, int device, bool seq,
-                   bool reg2, UnitCtx* u, int* variant, size_t* lds, int* block);
+                   bool reg2, bool few, UnitCtx* u, int* variant, size_t* lds, int* block);
 // One persistent resident launch over the shots of several items of one
 // code and parameters (items [nitems] in device memory, total shots in
 // all); ws holds the shot queue (resident_workspace_bytes). With a fail
@@ -220,9 +223,12 @@ bool batch_variant(const DevCode& c, int bp, const laim_resident_cfg* want, int 
 hipError_t launch_resident_group(const DevCode& c, const KParams& kp, const ResidentShape& sh,
                                  const GroupItemDev* items, int32_t nitems, int32_t total, void* ws,
                                  hipStream_t st);
+// units and reqs are read from (pinned) host memory; each block copies its
+// requests to reqs_dev first
 hipError_t launch_server(int bp, const BatchItemDev* items, const ServerUnitDev* units,
-                         int32_t nunits, const ServerReqDev* reqs, size_t lds, int block,
+                         int32_t nunits, const ServerReqDev* reqs, ServerReqDev* reqs_dev, size_t lds, int block,
                          hipStream_t st);
+int device_cus(int device);  // compute units
 
 // ---- continuous-time machine (laim_ctm.hip)
 struct CtmParamsDev {

@@ -293,6 +293,7 @@ __host__ __device__ constexpr int tile_partner(int k, int g) {
 // What one group of a unit works on.
 struct GroupJob {
   int32_t alive;
+  int32_t last;          // server: the last round of the request's budget
   int32_t r0;            // number of the first round run here (Philox counter)
   uint64_t shot;         // logical shot id
   const uint8_t* e0row;  // [n] initial error
@@ -334,6 +335,7 @@ struct BoolTag {
 __device__ __forceinline__ GroupJob dead_job() {
   GroupJob j;
   j.alive = 0;
+  j.last = 0;
   j.r0 = 0;
   j.shot = 0;
   j.e0row = nullptr;
@@ -1122,7 +1124,10 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
   asm volatile("" : "+v"(g_res));
   if (alive) {
     const GroupJob job = job_at(g_res);
-    if (job.z_out) {
+    // (the server takes z and s of a request only when it finishes)
+    bool out_zs = true;
+    if constexpr (Src::kServer) out_zs = !working || job.last;
+    if (job.z_out && out_zs) {
       uint8_t* zrow = job.z_out;
       if ((c.n & 15) == 0 && (reinterpret_cast<uintptr_t>(zrow) & 15) == 0) {
         // 16 bytes per thread from 16 bits of the bitmap
@@ -1137,7 +1142,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
         for (int32_t v = t; v < c.n; v += u.nt) zrow[v] = (uint8_t)((zw[v >> 5] >> (v & 31)) & 1u);
       }
     }
-    if (job.s_out) {
+    if (job.s_out && out_zs) {
 #pragma unroll 1
       for (int k = 0; k < CPT; ++k)
         if (t + k * u.nt < c.m) job.s_out[own_ch(k)] = (uint8_t)((sb >> k) & 1u);
@@ -1228,6 +1233,7 @@ struct ResArgs {
 };
 
 struct ResJobs {
+  static constexpr bool kServer = false;
   // copied by value: taking the address of a kernel argument would force it
   // into scratch memory
   const GroupItemDev* items;
@@ -1330,8 +1336,9 @@ __global__ void zero_u32_kernel(uint32_t* p, int32_t k) {
 
 // ---- serving: one round for every scheduled request, state in HBM
 struct ServerJobs {
+  static constexpr bool kServer = true;
   const ServerReqDev* R;
-  int32_t first, count;
+  int32_t first, count, n;
   bool given;
   __device__ bool next(int32_t*) {  // a single unit
     const bool once = !given;
@@ -1352,6 +1359,9 @@ struct ServerJobs {
     j.st_hdr = q.hdr;
     j.f_out = q.fail;
     j.ev_out = q.ev;
+    j.last = q.last;
+    j.z_out = q.res;
+    j.s_out = q.res ? q.res + n : nullptr;
     return j;
   }
 };
@@ -1382,10 +1392,20 @@ static const int kBatchVariants[][4] = {  // dc, dv, cpt, regular
 template <int BP>
 __global__ void __launch_bounds__(1024) server_kernel(const BatchItemDev* items,
                                                       const ServerUnitDev* units,
-                                                      const ServerReqDev* reqs, int32_t ctrl_off) {
+                                                      const ServerReqDev* reqs_host, ServerReqDev* reqs,
+                                                      int32_t ctrl_off) {
   extern __shared__ __align__(16) unsigned char smem[];
   int32_t* ctrl = reinterpret_cast<int32_t*>(smem + ctrl_off);
   const ServerUnitDev U = units[bid_x()];
+  // The step's tables stay in pinned host memory (a copy per table and step
+  // cost 3.4 us of a 100 us step each, and as much again between kernels);
+  // the block reads its own requests from there once, in one round trip.
+  {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(reqs_host + U.first);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(reqs + U.first);
+    for (int32_t i = tid_x(); i < U.count * (int32_t)(sizeof(ServerReqDev) / 4); i += bdim_x()) dst[i] = src[i];
+  }
+  __syncthreads();
   const BatchItemDev* I = items + U.item;
   const DevCode c = I->c;
   const KParams kp = I->kp;
@@ -1393,7 +1413,7 @@ __global__ void __launch_bounds__(1024) server_kernel(const BatchItemDev* items,
   ctx.rounds = U.rounds;
   ctx.resume = U.resume;
   ctx.events = 1;
-  ServerJobs jobs{reqs, U.first, U.count, false};
+  ServerJobs jobs{reqs, U.first, U.count, c.n, false};
 #define LAIM_CALL(DC, DV, CPT, BPV, REG) run_units<DC, DV, CPT, BPV, REG>(c, kp, ctx, jobs, smem, ctrl)
   LAIM_BATCH_SWITCH(I->variant, BP, LAIM_CALL)
 #undef LAIM_CALL
@@ -1473,7 +1493,7 @@ static size_t group_bytes_for(int dc, int mpad, int n, int m, bool seq) {
 }
 
 // Compute units of a device (256 if it cannot be asked).
-static int device_cus(int device) {
+int device_cus(int device) {
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) cus = 256;
   return cus;
@@ -1648,9 +1668,9 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
 // launch shape follows the code's resident shape, with checks per thread
 // limited to the compiled variants (at most the shape's value).
 bool batch_variant(const DevCode& c, int bp, const laim_resident_cfg* want, int device, bool seq,
-                   bool reg2, UnitCtx* u, int* variant, size_t* lds, int* block) {
+                   bool reg2, bool few, UnitCtx* u, int* variant, size_t* lds, int* block) {
   ResidentShape sh;
-  if (!resident_shape(c, bp, want, &sh, device, seq, reg2)) return false;
+  if (!resident_shape(c, bp, want, &sh, device, seq, reg2, few ? 1 : 0)) return false;
   const int dc = sh.dc, dv = sh.dv, reg = sh.reg;
   int best = -1;
   for (int i = 0; i < (int)(sizeof(kBatchVariants) / sizeof(kBatchVariants[0])); ++i) {
@@ -1680,7 +1700,7 @@ bool batch_variant(const DevCode& c, int bp, const laim_resident_cfg* want, int 
 }
 
 hipError_t launch_server(int bp, const BatchItemDev* items, const ServerUnitDev* units,
-                         int32_t nunits, const ServerReqDev* reqs, size_t lds, int block,
+                         int32_t nunits, const ServerReqDev* reqs, ServerReqDev* reqs_dev, size_t lds, int block,
                          hipStream_t st) {
   if (nunits <= 0) return hipSuccess;
   const void* fn = bp ? reinterpret_cast<const void*>(server_kernel<1>)
@@ -1691,9 +1711,11 @@ hipError_t launch_server(int bp, const BatchItemDev* items, const ServerUnitDev*
   }
   const int32_t ctrl_off = (int32_t)(lds - kCtrlWords * 4);
   if (bp)
-    hipLaunchKernelGGL(server_kernel<1>, dim3(nunits), dim3(block), lds, st, items, units, reqs, ctrl_off);
+    hipLaunchKernelGGL(server_kernel<1>, dim3(nunits), dim3(block), lds, st, items, units, reqs, reqs_dev,
+                       ctrl_off);
   else
-    hipLaunchKernelGGL(server_kernel<0>, dim3(nunits), dim3(block), lds, st, items, units, reqs, ctrl_off);
+    hipLaunchKernelGGL(server_kernel<0>, dim3(nunits), dim3(block), lds, st, items, units, reqs, reqs_dev,
+                       ctrl_off);
   return hipGetLastError();
 }
 

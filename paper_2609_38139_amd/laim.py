@@ -589,6 +589,11 @@ class Server:
         self.handle = h
         self.max_slots = max_slots
         self._ev = (ServerEvent * max_slots)()
+        self._evv = np.frombuffer(self._ev, dtype=np.dtype(
+            {"names": [f[0] for f in ServerEvent._fields_],
+             "formats": [np.dtype(f[1]) for f in ServerEvent._fields_],
+             "offsets": [getattr(ServerEvent, f[0]).offset for f in ServerEvent._fields_],
+             "itemsize": C.sizeof(ServerEvent)}))  # the same memory as rows
         self._codes = {}
 
     def submit(self, code: Code, params: DecodeParams, shot_id: int, e0=None, p: float = 0.0) -> int:
@@ -614,13 +619,8 @@ class Server:
         k = self.max_slots if max_events is None else min(int(max_events), self.max_slots)
         n = C.c_int32()
         check(lib().laim_server_step(self.handle, self._ev, k, C.byref(n)), "laim_server_step")
-        out = []
-        for i in range(n.value):
-            e = self._ev[i]
-            out.append({"ticket": e.ticket, "round": e.round, "done": bool(e.done), "tclr": e.tclr,
-                        "flips": e.flips, "defects": e.defects, "fail": e.fail,
-                        "latency_ns": e.latency_ns})
-        return out
+        return [{"ticket": t, "round": r, "done": d != 0, "tclr": c, "flips": f, "defects": w, "fail": x,
+                 "latency_ns": ns} for t, r, d, c, f, w, x, ns in self._evv[:n.value].tolist()]
 
     def result(self, ticket: int) -> dict:
         code = self._codes.pop(ticket)
