@@ -72,6 +72,37 @@ __device__ __forceinline__ float min3_abs(float a, float b, float c) {
   return r;
 }
 
+// ex[j] = the smallest |x[i]| over i != j, exactly (a minimum rounds nothing, so
+// any grouping gives the same value). Checks of degree 6 and 8 take the minima
+// of pairs, and of pairs of pairs, and one three-input minimum per output: 9
+// and 14 instructions against 12 and 18 for prefix and suffix minima.
+template <int DC>
+__device__ __forceinline__ void min_others(const float* x, float* ex) {
+  if constexpr (DC == 2) {
+    ex[0] = fabsf(x[1]);
+    ex[1] = fabsf(x[0]);
+  } else if constexpr (DC == 4) {
+    ex[0] = min3_abs(x[1], x[2], x[3]);
+    ex[1] = min3_abs(x[0], x[2], x[3]);
+    ex[2] = min3_abs(x[0], x[1], x[3]);
+    ex[3] = min3_abs(x[0], x[1], x[2]);
+  } else {
+    static_assert(DC == 6 || DC == 8, "compiled check degrees");
+    float p[DC / 2];
+#pragma unroll
+    for (int i = 0; i < DC / 2; ++i) p[i] = fminf(fabsf(x[2 * i]), fabsf(x[2 * i + 1]));
+#pragma unroll
+    for (int i = 0; i < DC / 2; ++i) {
+      // the other pairs' minimum: two pairs as they are (degree 6), or the
+      // pair beside this one and the two of the other half (degree 8)
+      const float a = DC == 6 ? p[(i + 1) % 3] : p[i ^ 1];
+      const float b = DC == 6 ? p[(i + 2) % 3] : fminf(p[(i & 2) ^ 2], p[((i & 2) ^ 2) + 1]);
+      ex[2 * i] = min3_abs(x[2 * i + 1], a, b);
+      ex[2 * i + 1] = min3_abs(x[2 * i], a, b);
+    }
+  }
+}
+
 // a ^ b ^ c in one v_bitop3_b32 (truth table 0x96).
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
   uint32_t r;

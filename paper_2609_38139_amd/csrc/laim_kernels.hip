@@ -741,27 +741,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
                 if (DC & 1) par ^= __float_as_uint(x[k][DC - 1]);
                 const float alpha_s = __uint_as_float(__float_as_uint(kp.alpha) ^ (par & 0x80000000u));
                 float ex[DC];  // smallest |m| over the other inputs
-                if (DC == 2) {
-                  ex[0] = fabsf(x[k][1]);
-                  ex[1] = fabsf(x[k][0]);
-                } else if (DC == 4) {
-                  ex[0] = min3_abs(x[k][1], x[k][2], x[k][3]);
-                  ex[1] = min3_abs(x[k][0], x[k][2], x[k][3]);
-                  ex[2] = min3_abs(x[k][0], x[k][1], x[k][3]);
-                  ex[3] = min3_abs(x[k][0], x[k][1], x[k][2]);
-                } else {
-                  float pre[DC], suf[DC];
-                  pre[1] = fabsf(x[k][0]);
-#pragma unroll
-                  for (int j = 2; j < DC; ++j) pre[j] = fminf(pre[j - 1], fabsf(x[k][j - 1]));
-                  suf[DC - 2] = fabsf(x[k][DC - 1]);
-#pragma unroll
-                  for (int j = DC - 3; j >= 0; --j) suf[j] = fminf(suf[j + 1], fabsf(x[k][j + 1]));
-                  ex[0] = suf[0];
-                  ex[DC - 1] = pre[DC - 1];
-#pragma unroll
-                  for (int j = 1; j < DC - 1; ++j) ex[j] = fminf(pre[j], suf[j]);
-                }
+                min_others<DC>(x[k], ex);
 #pragma unroll
                 for (int j = 0; j < DC; ++j) {
                   // With degree >= 2 there is an input to take the minimum of,

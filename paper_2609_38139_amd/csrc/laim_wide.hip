@@ -98,24 +98,7 @@ __device__ __forceinline__ void wide_check_rule(const KParams& kp, const float* 
     for (int j = 0; j + 1 < DC; j += 2) par = xor3(par, __float_as_uint(x[j]), __float_as_uint(x[j + 1]));
     const float alpha_s = __uint_as_float(__float_as_uint(kp.alpha) ^ (par & 0x80000000u));
     float ex[DC];  // smallest |m| over the other inputs
-    if constexpr (DC == 4) {
-      ex[0] = min3_abs(x[1], x[2], x[3]);
-      ex[1] = min3_abs(x[0], x[2], x[3]);
-      ex[2] = min3_abs(x[0], x[1], x[3]);
-      ex[3] = min3_abs(x[0], x[1], x[2]);
-    } else {
-      float pre[DC], suf[DC];
-      pre[1] = fabsf(x[0]);
-#pragma unroll
-      for (int j = 2; j < DC; ++j) pre[j] = fminf(pre[j - 1], fabsf(x[j - 1]));
-      suf[DC - 2] = fabsf(x[DC - 1]);
-#pragma unroll
-      for (int j = DC - 3; j >= 0; --j) suf[j] = fminf(suf[j + 1], fabsf(x[j + 1]));
-      ex[0] = suf[0];
-      ex[DC - 1] = pre[DC - 1];
-#pragma unroll
-      for (int j = 1; j < DC - 1; ++j) ex[j] = fminf(pre[j], suf[j]);
-    }
+    min_others<DC>(x, ex);
 #pragma unroll
     for (int j = 0; j < DC; ++j) {
       const float v = alpha_s * ex[j];
