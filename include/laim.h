@@ -249,7 +249,10 @@ laim_status laim_decode_rounds(const laim_code* code, const laim_decode_params* 
                                float* L_out, int32_t* sweeps_out, uint8_t* fail_out, int32_t form,
                                laim_stream stream);
 
-/* Launch shape of the resident form (0 in a field means: choose). */
+/* Launch shape of the resident form (0 in a field means: choose). With
+ * sum-product on regular codes of check degree 4 or 6, twice as many threads
+ * per shot as its checks need, 2 ceil(m / checks_per_thread), put every check
+ * on two of them. */
 typedef struct {
   int32_t threads_per_shot; /* threads cooperating on one shot */
   int32_t checks_per_thread;

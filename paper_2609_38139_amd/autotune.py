@@ -47,15 +47,17 @@ def candidates(code, bp: str):
     from . import laim
     out = []
     for cpt in (1, 2, 4, 8):
-        for spb in (0, 1, 2, 4, 8):
-            cfg = {"checks_per_thread": cpt, "shots_per_block": spb}
-            try:
-                code.set_resident_cfg(bp, cfg)
-                got = code.resident_cfg(bp)
-            except laim.LaimError:
-                continue
-            if got not in out:
-                out.append(got)
+        # sum-product also with two threads per check
+        for nt in (0, 2 * -(-code.m // cpt)) if bp == "sumproduct" else (0,):
+            for spb in (0, 1, 2, 4, 8):
+                cfg = {"threads_per_shot": nt, "checks_per_thread": cpt, "shots_per_block": spb}
+                try:
+                    code.set_resident_cfg(bp, cfg)
+                    got = code.resident_cfg(bp)
+                except laim.LaimError:
+                    continue
+                if got not in out:
+                    out.append(got)
     code.set_resident_cfg(bp, None)
     return out
 

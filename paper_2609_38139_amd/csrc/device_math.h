@@ -315,16 +315,72 @@ __device__ __forceinline__ void boxplus_folds(const float* x, float* acc) {
 // wavefront-checks of the 2D toric code L = 32 at p = 0.05, and in 71% of
 // those of the [[144,12,12]] code at p = 0.03.
 template <int D>
-__device__ __forceinline__ void boxplus_all(const float* x, float* acc) {
+__device__ constexpr float box_far_bound() {
   constexpr float kLn[] = {0.0f, 0.0f, 0.0f, 0.694f, 1.099f, 1.387f, 1.610f, 1.792f, 1.946f};
-  constexpr float bound = kBoxFar + kLn[D] + 0.01f;
+  return kBoxFar + kLn[D] + 0.01f;
+}
+template <int D>
+__device__ __forceinline__ void boxplus_all(const float* x, float* acc) {
   float mn = fabsf(x[0]);
 #pragma unroll
   for (int k = 1; k < D; ++k) mn = fminf(mn, fabsf(x[k]));
-  if (D > 2 && __builtin_amdgcn_ballot_w64(mn < bound) == 0ull)
+  if (D > 2 && __builtin_amdgcn_ballot_w64(mn < box_far_bound<D>()) == 0ull)
     boxplus_folds<D, true>(x, acc);
   else
     boxplus_folds<D, false>(x, acc);
+}
+
+// The check rule with a check on two neighbouring lanes (an even and an odd
+// one), for launches that leave most of the device idle: each lane forms half of
+// the D outputs and the folds that they need. The even lane works on
+// y_j = x_j, the odd one on y_j = x_{D-1-j}; box-plus is symmetric in its two
+// arguments bit for bit, so with G_0 = y_0, G_i = G_{i-1} [+] y_i the even
+// lane's G_i are the prefix folds F_i and the odd lane's the suffix folds
+// B_{D-1-i}. Output j >= D / 2 (counted in y) is G_{j-1} [+] P_{D-2-j}, P the
+// neighbour's folds, and the last one G_{D-2}. y[0 .. D / 2): this lane's
+// inputs; out[i]: output D / 2 + i. 3 (D - 2) / 2 box-plus steps per lane and
+// D - 2 stages of one or two, against stages of two or four with one lane per
+// check.
+__device__ __forceinline__ float pair_swap(float x) {  // the neighbour's value (lanes 2i and 2i + 1)
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));
+}
+template <int D, bool FAR, int S>
+__device__ __forceinline__ void boxplus_pair_stage(const float* y, float* G, float* out) {
+  if constexpr (S <= D - 2) {
+    if constexpr (S < D / 2) {
+      boxplus<FAR, 1>(&G[S - 1], &y[S], &G[S]);
+    } else {
+      const float a[2] = {G[S - 1], G[S - 1]}, b[2] = {y[S], pair_swap(G[D - 2 - S])};
+      float o[2];
+      boxplus<FAR, 2>(a, b, o);
+      G[S] = o[0];
+      out[S - D / 2] = o[1];
+    }
+    boxplus_pair_stage<D, FAR, S + 1>(y, G, out);
+  }
+}
+template <int D, bool FAR>
+__device__ __forceinline__ void boxplus_pair_folds(const float* y, float* out) {
+  float G[D];
+  G[0] = y[0] + 0.0f;
+  boxplus_pair_stage<D, FAR, 1>(y, G, out);
+  out[D / 2 - 1] = G[D - 2];
+}
+template <int D>
+__device__ __forceinline__ void boxplus_pair(const float* half, float* out) {
+  static_assert(D == 4 || D == 6, "even degrees with a box-plus step");
+  float y[D];
+  float mn = fabsf(half[0]);
+#pragma unroll
+  for (int j = 0; j < D / 2; ++j) {
+    y[j] = half[j];
+    y[D - 1 - j] = pair_swap(half[j]);
+    mn = fminf(mn, fabsf(half[j]));
+  }
+  if (__builtin_amdgcn_ballot_w64(mn < box_far_bound<D>()) == 0ull)
+    boxplus_pair_folds<D, true>(y, out);
+  else
+    boxplus_pair_folds<D, false>(y, out);
 }
 
 // The folds of a check of degree deg in a variant with DC slots (REG: deg =

@@ -99,6 +99,7 @@ struct ResidentShape {
   size_t lds;    // dynamic LDS bytes per block
   int32_t dc, dv, reg;  // kernel variant degrees (reg: exact regular variant)
   int32_t tile = 0;     // the tiled variant (2D toric layout, min-sum, 8 checks per thread)
+  int32_t lpc = 1;      // lanes per check (2: nt / 2 lane pairs share the checks)
 };
 
 // Whether the exact-degree kernels for qubit degree 2 may run: they skip the

@@ -378,11 +378,18 @@ __device__ __forceinline__ uint32_t spread4(uint32_t nib) { return (nib * 0x0020
 // code and launch shape: the per-thread graph tables are built once and
 // stay in registers. Every thread of the block calls it (threads beyond
 // spb * nt only take part in the barriers).
-template <int DC, int DV, int CPT, int BP, bool REG, class Src, bool TILE = false>
+// LPC: lanes per check. With 2 (sum-product, for launches that leave most of the
+// device idle) the lanes 2 i and 2 i + 1 of a group share the checks i + k nt / 2:
+// both keep their syndrome bits, each gathers and sends half of the messages,
+// and the even one handles the feedback and the outputs.
+template <int DC, int DV, int CPT, int BP, bool REG, class Src, bool TILE = false, int LPC = 1>
 __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u, Src& src,
                           unsigned char* smem, int32_t* ctrl) {
   static_assert(!TILE || (DC == 4 && DV == 2 && CPT == 8 && BP == 0 && REG),
                 "the tiled variant is min-sum on the 2D toric layout");
+  static_assert(LPC == 1 || (LPC == 2 && BP == 1 && REG && !TILE && (DC == 4 || DC == 6)),
+                "two lanes per check: sum-product on regular codes");
+  constexpr int HD = DC / LPC;  // inputs that a lane gathers and outputs that it sends, per check
   const int32_t spb = u.spb;
   const int32_t tid = tid_x();
   const int32_t g = tid / u.nt;
@@ -411,11 +418,18 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
   const int32_t tile0 = (TILE && member) ? c.tile_chk[t] : 0;
   // Recomputed where used (one or two instructions) rather than kept for
   // every k: registers are the resident kernels' limit.
+  const int32_t tc = LPC == 2 ? t >> 1 : t;            // this thread's check 0,
+  const int32_t ntc = LPC == 2 ? u.nt >> 1 : u.nt;     // and the step to its next
+  const int32_t odd = LPC == 2 ? t & 1 : 0;
+  const bool lead = LPC == 1 || !odd;
   auto own_ch = [&](int32_t k) -> int32_t {
-    int32_t b = TILE ? tile0 : t;
+    int32_t b = TILE ? tile0 : tc;
     asm volatile("" : "+v"(b));
-    return TILE ? b + (k >> 2) * c.tile_L + (k & 3) : b + k * u.nt;
+    return TILE ? b + (k >> 2) * c.tile_L + (k & 3) : b + k * ntc;
   };
+  // the slot of a lane's input j, and of its output j
+  auto in_slot = [&](int j) -> int32_t { return LPC == 2 ? (odd ? DC - 1 - j : j) : j; };
+  auto out_slot = [&](int j) -> int32_t { return LPC == 2 ? (odd ? HD - 1 - j : HD + j) : j; };
 
   auto mword = [&](int32_t ch, int32_t j) -> int32_t {
     return TILE ? c.tile_word[ch * DC + j] : msg_word<DC>(ch, j);
@@ -430,18 +444,18 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
   // direction j, whose row slot is tile_jo; pidx of an input inside the tile
   // is not used.
   int32_t deg[CPT];
-  int32_t pidx[CPT][DC][DV > 1 ? DV - 1 : 1];
+  int32_t pidx[CPT][HD][DV > 1 ? DV - 1 : 1];
   uint32_t vmask = 0u;  // bit k: check k of this thread is one of the code's checks
 #pragma unroll
   for (int k = 0; k < CPT; ++k) {
-    const int32_t vk = t + k * u.nt;
+    const int32_t vk = tc + k * ntc;
     const bool valid = member && vk < c.m;
     const int32_t ch = (TILE && valid) ? own_ch(k) : vk;
     vmask |= (valid ? 1u : 0u) << k;
     deg[k] = (valid && !REG) ? c.chk_deg[ch] : DC;
 #pragma unroll
-    for (int j = 0; j < DC; ++j) {
-      const int32_t jr = (TILE && valid) ? c.tile_jo[vk * DC + j] : j;
+    for (int j = 0; j < HD; ++j) {
+      const int32_t jr = (TILE && valid) ? c.tile_jo[vk * DC + j] : in_slot(j);
 #pragma unroll
       for (int p = 0; p < DV - 1; ++p) {
         int32_t e = -1;
@@ -489,7 +503,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
     }
 #pragma unroll 1
     for (int k = 0; k < CPT; ++k) {
-      const int32_t ch = t + k * u.nt;  // no resume in the tiled variant: its LDS index
+      const int32_t ch = tc + k * ntc;  // no resume in the tiled variant: its LDS index
       float* mk = msg + msg_word<DC>(ch, 0);
       if (!TILE && u.resume && alive && ch < c.m) {
         for (int j = 0; j < DC; ++j)
@@ -543,7 +557,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
     } else {
 #pragma unroll 1
       for (int k = 0; k < CPT; ++k) {
-        if (t + k * u.nt >= c.m) continue;
+        if (tc + k * ntc >= c.m) continue;
         const int32_t ch = own_ch(k);
         const uint32_t x = u.resume ? job.st_s[ch] : job.s0row[ch];
         sb |= (x & 1u) << k;
@@ -631,7 +645,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
 #pragma unroll
           for (int k = 0; k < CPT; ++k) {
             const float z0 = (((sb >> k) ^ (uint32_t)DC) & 1u) ? -0.0f : 0.0f;
-            float* mk = msg + msg_word<DC>(t + k * u.nt, 0);  // LDS index of check k
+            float* mk = msg + msg_word<DC>(tc + k * ntc, 0);  // LDS index of check k
 #pragma unroll
             for (int j = 0; j < DC; ++j) {
               mk[j * kSlotStride] = z0;
@@ -652,7 +666,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
         for (int k = 0; k < CPT; ++k)
 #pragma unroll
           for (int j = 0; j < DC; ++j)
-            if (tile_partner(k, j) >= 0) io[TILE ? k : 0][j] = msg[msg_word<DC>(t + k * u.nt, j)];
+            if (tile_partner(k, j) >= 0) io[TILE ? k : 0][j] = msg[msg_word<DC>(tc + k * ntc, j)];
       }
       // With CMP, a sweep may also compare each new message with the one
       // it replaces; comparing costs half a sweep's worth of extra VALU per
@@ -670,18 +684,18 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
           const bool CMP = CMP_ON && ((it & 7) == 7 || it == kp.iters - 1);
           const int32_t f = ncmp & 1;
           const bool first = fresh;
-          float x[CPT][DC];
+          float x[CPT][HD];
           if (sweep) {
             if (!REG && fresh) {
 #pragma unroll
               for (int k = 0; k < CPT; ++k)
 #pragma unroll
-                for (int j = 0; j < DC; ++j) x[k][j] = (j >= deg[k]) ? __builtin_inff() : 0.0f;
+                for (int j = 0; j < HD; ++j) x[k][j] = (j >= deg[k]) ? __builtin_inff() : 0.0f;
             } else {
 #pragma unroll
               for (int k = 0; k < CPT; ++k) {
 #pragma unroll
-                for (int j = 0; j < DC; ++j) {
+                for (int j = 0; j < HD; ++j) {
                   // (inside a tile the input is formed after the barrier,
                   // from a register)
                   if (TILE && tile_partner(k, j) >= 0) continue;
@@ -726,8 +740,8 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
                 }
               }
               const uint32_t sigma_neg = ((sb >> k) ^ (uint32_t)(REG ? DC : deg[k])) & 1u;
-              float out[DC];
-              if (BP == 0) {
+              float out[HD];
+              if constexpr (BP == 0) {
                 // normalised min-sum: alpha * (smallest other |m|) with the
                 // sign product. No input is -0 (pi + messages with pi != -0,
                 // or +0 on a fresh sweep), so the sign bit is sg(). The sign
@@ -755,27 +769,31 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
                 }
               } else {
                 // sum-product: box-plus of the other inputs (prefix/suffix folds)
-                float acc[DC];
-                boxplus_others<DC, REG>(x[k], deg[k], acc);
+                float acc[HD];
+                if constexpr (LPC == 2)
+                  boxplus_pair<DC>(x[k], acc);
+                else
+                  boxplus_others<DC, REG>(x[k], deg[k], acc);
 #pragma unroll
-                for (int j = 0; j < DC; ++j) out[j] = __builtin_amdgcn_fmed3f(sigma_neg ? -acc[j] : acc[j], -C, C);
+                for (int j = 0; j < HD; ++j) out[j] = __builtin_amdgcn_fmed3f(sigma_neg ? -acc[j] : acc[j], -C, C);
               }
-              float* mk = msg + msg_word<DC>(t + k * u.nt, 0);
+              float* mk = msg + msg_word<DC>(tc + k * ntc, 0);
               if (CMP) {  // padding checks and the padding slots of irregular checks are never read
                 uint32_t dk = 0u;
 #pragma unroll
-                for (int j = 0; j < DC; ++j) {
-                  const float old = (TILE && tile_partner(k, j) >= 0) ? io[TILE ? k : 0][j] : mk[j * kSlotStride];
+                for (int j = 0; j < HD; ++j) {
+                  const float old =
+                      (TILE && tile_partner(k, j) >= 0) ? io[TILE ? k : 0][j] : mk[out_slot(j) * kSlotStride];
                   if (REG || j < deg[k]) dk |= __float_as_uint(old) ^ __float_as_uint(out[j]);
                 }
                 diff |= ((vmask >> k) & 1u) ? dk : 0u;
               }
 #pragma unroll
-              for (int j = 0; j < DC; ++j) {
+              for (int j = 0; j < HD; ++j) {
                 if (TILE && tile_partner(k, j) >= 0)
                   io[TILE ? k : 0][j] = out[j];  // read from a register within the tile
                 else
-                  mk[j * kSlotStride] = out[j];
+                  mk[out_slot(j) * kSlotStride] = out[j];
               }
             }
           }
@@ -809,7 +827,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
           for (int k = 0; k < CPT; ++k)
 #pragma unroll
             for (int j = 0; j < DC; ++j)
-              if (tile_partner(k, j) >= 0) msg[msg_word<DC>(t + k * u.nt, j)] = io[TILE ? k : 0][j];
+              if (tile_partner(k, j) >= 0) msg[msg_word<DC>(tc + k * ntc, j)] = io[TILE ? k : 0][j];
         }
         __syncthreads();
       }
@@ -829,7 +847,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
     uint32_t reqm = 0;  // this thread's checks with a recorded request (sequential rule)
     if (working) {
       if (!same_state) noev = 0u;
-      uint32_t act = sb & ~noev;
+      uint32_t act = lead ? sb & ~noev : 0u;
       int32_t nflip = 0;
       // regular codes with qubits of degree 2: the qubits of an active check
       // and the other check of each are read together (one round trip), and
@@ -984,7 +1002,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
         }
       }
       if (nflip) atomicAdd(&gw[kGwFlips], nflip);
-      if (sb & ~noev) gw[kGwLive] = 1;  // an active check passed the Evidence test
+      if (lead && (sb & ~noev)) gw[kGwLive] = 1;  // an active check passed the Evidence test
     }
     if (kp.conflict == kConflictSequential) {
       // Sequential rule: request i applies iff its check's start syndrome
@@ -1125,7 +1143,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
     if (job.s_out && out_zs) {
 #pragma unroll 1
       for (int k = 0; k < CPT; ++k)
-        if (t + k * u.nt < c.m) job.s_out[own_ch(k)] = (uint8_t)((sb >> k) & 1u);
+        if (lead && tc + k * ntc < c.m) job.s_out[own_ch(k)] = (uint8_t)((sb >> k) & 1u);
     }
     if (job.t_out && t == 0) job.t_out[0] = tclr;
     if (job.sw_out && t == 0) job.sw_out[0] = nsweeps;
@@ -1144,7 +1162,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
     if (job.st_msg) {
 #pragma unroll 1
       for (int k = 0; k < CPT; ++k) {
-        if (t + k * u.nt >= c.m) continue;
+        if (tc + k * ntc >= c.m) continue;
         const int32_t ch = own_ch(k);
         for (int j = 0; j < c.dcmax && j < DC; ++j)
           job.st_msg[(int64_t)ch * c.dcmax + j] = msg[mword(ch, j)];
@@ -1175,7 +1193,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
       for (int w = 0; w < kFusedMaxWords; ++w)
         if (lp[w]) atomicXor(reinterpret_cast<uint32_t*>(&gw[kGwLpar + w]), lp[w]);
     }
-    if (job.ev_out && sb) atomicAdd(&gw[kGwDefects], __popc(sb));
+    if (job.ev_out && sb && lead) atomicAdd(&gw[kGwDefects], __popc(sb));
   }
   __syncthreads();
   if (alive && t == 0) {
@@ -1281,7 +1299,7 @@ struct ResJobs {
   }
 };
 
-template <int DC, int DV, int CPT, int BP, bool REG, bool TILE>
+template <int DC, int DV, int CPT, int BP, bool REG, bool TILE, int LPC = 1>
 __device__ __forceinline__ void resident_body(const DevCode& c, const KParams& kp, const ResArgs& a) {
   extern __shared__ __align__(16) unsigned char smem[];
   // control words after the groups, so that group 0's messages start at
@@ -1289,12 +1307,17 @@ __device__ __forceinline__ void resident_body(const DevCode& c, const KParams& k
   int32_t* ctrl = reinterpret_cast<int32_t*>(smem + (size_t)a.u.spb * a.u.group_bytes);
   ResJobs jobs{a.items, a.nitems, a.e0,     a.s0,     a.r0,      a.shot0,   a.nshots, c.n, c.m, -1,
                a.z,     a.s,      a.tclr,   a.L,      a.fail,    a.sweeps,  a.counter, a.u.spb};
-  run_units<DC, DV, CPT, BP, REG, ResJobs, TILE>(c, kp, a.u, jobs, smem, ctrl);
+  run_units<DC, DV, CPT, BP, REG, ResJobs, TILE, LPC>(c, kp, a.u, jobs, smem, ctrl);
 }
 
 template <int DC, int DV, int CPT, int BP, bool REG>
 __global__ void __launch_bounds__(1024) resident_kernel(DevCode c, KParams kp, ResArgs a) {
   resident_body<DC, DV, CPT, BP, REG, false>(c, kp, a);
+}
+
+template <int DC, int DV, int CPT>
+__global__ void __launch_bounds__(1024) resident_pair_kernel(DevCode c, KParams kp, ResArgs a) {
+  resident_body<DC, DV, CPT, 1, true, false, 2>(c, kp, a);
 }
 
 // The tiled variant runs blocks of at most kTileMaxThreads threads with at
@@ -1405,6 +1428,7 @@ typedef void (*ResKernel)(DevCode, KParams, ResArgs);
 struct ResVariant {
   int dc, dv, cpt, bp, reg, tile;
   ResKernel fn;
+  int lpc = 1;  // lanes per check
 };
 
 #define LAIM_RES(DC, DV, CPT)                                                     \
@@ -1413,6 +1437,8 @@ struct ResVariant {
 #define LAIM_RES_IRR(DC, DV, CPT)                                                 \
   {DC, DV, CPT, 0, 0, 0, resident_kernel<DC, DV, CPT, 0, false>},                \
       {DC, DV, CPT, 1, 0, 0, resident_kernel<DC, DV, CPT, 1, false>}
+
+#define LAIM_RES_PAIR(DC, DV, CPT) {DC, DV, CPT, 1, 1, 0, resident_pair_kernel<DC, DV, CPT>, 2}
 
 static const ResVariant kResVariants[] = {
     LAIM_RES(2, 2, 1), LAIM_RES(2, 2, 2), LAIM_RES(2, 2, 4), LAIM_RES(2, 2, 8),
@@ -1423,6 +1449,10 @@ static const ResVariant kResVariants[] = {
     LAIM_RES_IRR(6, 2, 1), LAIM_RES_IRR(6, 2, 2), LAIM_RES_IRR(6, 2, 4), LAIM_RES_IRR(6, 2, 8),
     LAIM_RES_IRR(8, 4, 1), LAIM_RES_IRR(8, 4, 2), LAIM_RES_IRR(8, 4, 4),
     {4, 2, 8, 0, 1, 1, resident_tile_kernel},
+    LAIM_RES_PAIR(4, 2, 1), LAIM_RES_PAIR(4, 2, 2), LAIM_RES_PAIR(4, 2, 4),
+    LAIM_RES_PAIR(6, 2, 1), LAIM_RES_PAIR(6, 2, 2), LAIM_RES_PAIR(6, 2, 4),
+    LAIM_RES_PAIR(4, 4, 1), LAIM_RES_PAIR(4, 4, 2), LAIM_RES_PAIR(4, 4, 4),
+    LAIM_RES_PAIR(6, 3, 1), LAIM_RES_PAIR(6, 3, 2),
 };
 
 // Template degrees for a code: exact ones for the regular families, a
@@ -1456,9 +1486,10 @@ static bool pick_degrees(const DevCode& c, bool reg2, int* dc, int* dv, int* reg
   return false;
 }
 
-static const ResVariant* find_variant(int dc, int dv, int cpt, int bp, int reg, int tile = 0) {
+static const ResVariant* find_variant(int dc, int dv, int cpt, int bp, int reg, int tile = 0, int lpc = 1) {
   for (const auto& v : kResVariants)
-    if (v.dc == dc && v.dv == dv && v.cpt == cpt && v.bp == bp && v.reg == reg && v.tile == tile) return &v;
+    if (v.dc == dc && v.dv == dv && v.cpt == cpt && v.bp == bp && v.reg == reg && v.tile == tile && v.lpc == lpc)
+      return &v;
   return nullptr;
 }
 
@@ -1526,6 +1557,20 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
   return full;
 }
 
+// Whether the built-in rule puts a check on two lanes, one check per pair
+// (sum-product): shorter chains per lane for the same work in all. It pays
+// while wavefronts are few -- up to 8 per SIMD counted at one lane per check, and
+// blocks of at most 900 threads, past which one block alone keeps every SIMD
+// busy (ms at one and two lanes: 2D toric L = 16, 16 / 1,024 / 4,096 shots
+// 0.28 / 0.58 / 1.69 and 0.23 / 0.54 / 1.81; 3D point L = 8, 512 checks, 256 shots
+// 0.99 and 1.11) -- and on (6, 3) codes always: a few shots that never clear
+// set the end of a launch of their short shots ([[144,12,12]], 65,536 shots, p =
+// 0.03: 5.29 and 3.70; [[72,12,6]] 0.85 and 0.78).
+static bool pairs_pay(const DevCode& c, int bp, int dc, int dv, int reg, int64_t nshots, int cus) {
+  if (bp != 1 || 2 * c.m > 900 || !find_variant(dc, dv, 1, bp, reg, 0, 2)) return false;
+  return dv == 3 || (nshots > 0 && nshots * ((c.m + 63) / 64) <= (int64_t)8 * 4 * cus);
+}
+
 // Shots per block by the built-in rule: fills the wavefronts of a block of
 // at most 256 threads, the fewest shots first (each further one has to add 2%
 // of lanes in use: the shots of a block run in lockstep and wait for the
@@ -1564,7 +1609,17 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
   // min-sum on the 2D toric layout: the tiled variant, on a full device faster
   // than the other shapes at every L measured (8 to 64)
   const bool tile_ok = c.tile_chk && bp == 0 && dc == 4 && dv == 2 && reg && !seq;
-  if (cpt <= 0 && nt <= 0) cpt = built_in_cpt(c, bp, dc, dv, reg, tile_ok, nshots, device_cus(device));
+  int lpc = 1;
+  if (cpt <= 0 && nt <= 0) {
+    const int cus = device_cus(device);
+    cpt = built_in_cpt(c, bp, dc, dv, reg, tile_ok, nshots, cus);
+    if (pairs_pay(c, bp, dc, dv, reg, nshots, cus)) {
+      cpt = 1;
+      lpc = 2;
+    }
+  } else if (cpt > 0 && nt == 2 * ((c.m + cpt - 1) / cpt) && find_variant(dc, dv, cpt, bp, reg, 0, 2)) {
+    lpc = 2;  // two threads per check asked for
+  }
   if (cpt <= 0) {
     cpt = (c.m + nt - 1) / nt;
     int allowed[] = {1, 2, 4, 8};
@@ -1582,12 +1637,12 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
         }
     cpt = pick;
   }
-  if (!find_variant(dc, dv, cpt, bp, reg)) {
+  if (!find_variant(dc, dv, cpt, bp, reg, 0, lpc)) {
     set_error("no resident kernel for checks_per_thread = %d (degrees %d/%d)", cpt, dc, dv);
     return false;
   }
-  if (nt <= 0) nt = (c.m + cpt - 1) / cpt;
-  if (nt * cpt < c.m) {
+  if (nt <= 0) nt = lpc * ((c.m + cpt - 1) / cpt);
+  if (nt / lpc * cpt < c.m) {
     set_error("threads_per_shot * checks_per_thread = %d < m = %d", nt * cpt, c.m);
     return false;
   }
@@ -1610,7 +1665,7 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
   if (spb <= 0) {
     spb = built_in_spb(nt);
     // as many as the LDS holds (and not more than there are)
-    const size_t gb1 = group_bytes_for(dc, (nt * cpt + 63) / 64 * 64, c.n, c.m, seq);
+    const size_t gb1 = group_bytes_for(dc, (nt / lpc * cpt + 63) / 64 * 64, c.n, c.m, seq);
     while (spb > 1 && (kCtrlWords * 4 + gb1 * (size_t)spb > (size_t)lds_max || (nshots > 0 && spb > nshots))) --spb;
   }
   if (spb > kMaxShotsPerBlock) spb = kMaxShotsPerBlock;
@@ -1618,7 +1673,7 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
     set_error("block of %d threads exceeds 1024", nt * spb);
     return false;
   }
-  const int mpad = (nt * cpt + 63) / 64 * 64;
+  const int mpad = (nt / lpc * cpt + 63) / 64 * 64;
   const size_t gb = group_bytes_for(dc, mpad, c.n, c.m, seq);
   const size_t lds = kCtrlWords * 4 + gb * (size_t)spb;
   if (lds > (size_t)lds_max) {
@@ -1635,6 +1690,7 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
   out->dc = dc;
   out->dv = dv;
   out->reg = reg;
+  out->lpc = lpc;
   // the tiled variant: min-sum on the 2D toric layout with its shape (8
   // checks per thread, m / 8 threads per shot); the sequential rule keeps
   // the plain variant
@@ -1651,6 +1707,10 @@ bool batch_variant(const DevCode& c, int bp, const laim_resident_cfg* want, int 
                    bool reg2, bool few, UnitCtx* u, int* variant, size_t* lds, int* block) {
   ResidentShape sh;
   if (!resident_shape(c, bp, want, &sh, device, seq, reg2, few ? 1 : 0)) return false;
+  if (sh.lpc != 1) {  // (compiled with one lane per check only)
+    laim_resident_cfg one = {0, sh.cpt, want ? want->shots_per_block : 0};
+    if (!resident_shape(c, bp, &one, &sh, device, seq, reg2)) return false;
+  }
   const int dc = sh.dc, dv = sh.dv, reg = sh.reg;
   int best = -1;
   for (int i = 0; i < (int)(sizeof(kBatchVariants) / sizeof(kBatchVariants[0])); ++i) {
@@ -1728,7 +1788,7 @@ size_t resident_workspace_bytes() { return 256; }
 static hipError_t launch_resident_args(const DevCode& c, const KParams& kp, const ResidentShape& sh,
                                        ResArgs& a, int32_t total, hipStream_t st) {
   if (sh.reg && sh.dv == 2 && !reg_dv2_ok(kp)) return hipErrorInvalidValue;
-  const ResVariant* var = find_variant(sh.dc, sh.dv, sh.cpt, kp.bp, sh.reg, sh.tile);
+  const ResVariant* var = find_variant(sh.dc, sh.dv, sh.cpt, kp.bp, sh.reg, sh.tile, sh.lpc);
   if (!var) return hipErrorInvalidValue;
   a.u.nt = sh.nt;
   a.u.vpt = sh.vpt;

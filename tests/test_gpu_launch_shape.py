@@ -52,3 +52,31 @@ def test_results_do_not_depend_on_the_batch_size(L, orc, name, shape, bp, confli
         for k in ("z", "s", "tclr", "fail"):
             assert torch.equal(g[k], ref[k][:S]), (S, k)
         assert torch.equal(g["L"].view(torch.int32), ref["L"][:S].view(torch.int32)), S
+
+
+@pytest.mark.parametrize("cpt", [1, 2, 4])
+@pytest.mark.parametrize("name", ["toric2d:6", "toric2d:9", "bb:6x6", "toric3d_point:3", "toric3d_membrane:3"])
+def test_two_threads_per_check(L, orc, name, cpt):
+    """The pair kernels against the oracle, bit for bit: pairs that end inside a
+    wavefront, padding checks, several shots per block, every conflict rule and
+    priors on both sides of the short folds."""
+    import torch
+    spec = codes.by_name(name)
+    if cpt == 4 and name.startswith("bb"):
+        pytest.skip("not compiled for (6, 3)")
+    dc = L.Code(spec, 0)
+    nt = 2 * -(-spec.m // cpt)
+    e0 = (np.random.default_rng(2).random((61, spec.n)) < 0.05).astype(np.uint8)
+    for spb in (1, 3):
+        for k, (conflict, move) in enumerate([("or", "single"), ("xor", "multi"), ("sequential", "single")]):
+            for q in (0.05, 9e-5, 0.5):
+                P = dict(bp="sumproduct", q=q, rounds=4, iters=9, conflict=conflict, move=move, seed=k)
+                cfg = {"threads_per_shot": nt, "checks_per_thread": cpt, "shots_per_block": spb}
+                print(f"[pairs] {name} {cfg} {P}", flush=True)
+                g = L.decode_rounds(dc, L.DecodeParams(**P), torch.from_numpy(e0).cuda(), cfg=cfg, want_beliefs=True,
+                                    want_fail=True)
+                o = orc.decode(spec, orc.DecodeParams(**P), e0, want_beliefs=True)
+                for key in ("z", "s", "tclr"):
+                    assert np.array_equal(g[key].cpu().numpy(), o[key]), (spb, conflict, q, key)
+                assert np.array_equal(g["L"].cpu().numpy().view(np.uint32), o["L"].view(np.uint32)), (spb, conflict, q)
+                assert np.array_equal(g["fail"].cpu().numpy(), orc.logical_failure(spec, e0, o["z"]))
