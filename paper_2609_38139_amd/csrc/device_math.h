@@ -269,7 +269,8 @@ __device__ __forceinline__ float boxplus1(float a, float b) {
 // 3 (D - 2) box-plus steps in D - 2 stages of independent ones: stage S forms
 // F_S, B_{D-1-S} and the outputs whose two folds the stages before it made
 // (output j in stage max(j - 1, D - 2 - j) + 1: none, one or two a stage).
-template <int D, bool FAR, int S>
+// LEAN: at most two steps at a time, for kernels short of registers.
+template <int D, bool FAR, int S, bool LEAN>
 __device__ __forceinline__ void boxplus_stage(const float* x, float* F, float* B, float* acc) {
   if constexpr (S <= D - 2) {
     constexpr int hi = S, lo = D - 1 - S;  // this stage's outputs, from the middle stage on
@@ -288,20 +289,26 @@ __device__ __forceinline__ void boxplus_stage(const float* x, float* F, float* B
       a[3] = F[lo - 1];
       b[3] = B[lo + 1];
     }
-    boxplus<FAR, N>(a, b, o);
+    if constexpr (LEAN && N > 2) {
+      boxplus<FAR, 2>(a, b, o);
+      __builtin_amdgcn_sched_barrier(0);
+      boxplus<FAR, N - 2>(a + 2, b + 2, o + 2);
+    } else {
+      boxplus<FAR, N>(a, b, o);
+    }
     F[S] = o[0];
     B[D - 1 - S] = o[1];
     if constexpr (any) acc[hi] = o[2];
     if constexpr (both) acc[lo] = o[3];
-    boxplus_stage<D, FAR, S + 1>(x, F, B, acc);
+    boxplus_stage<D, FAR, S + 1, LEAN>(x, F, B, acc);
   }
 }
-template <int D, bool FAR>
+template <int D, bool FAR, bool LEAN>
 __device__ __forceinline__ void boxplus_folds(const float* x, float* acc) {
   float F[D], B[D];
   F[0] = x[0] + 0.0f;
   B[D - 1] = x[D - 1] + 0.0f;
-  boxplus_stage<D, FAR, 1>(x, F, B, acc);
+  boxplus_stage<D, FAR, 1, LEAN>(x, F, B, acc);
   acc[0] = B[1];
   acc[D - 1] = F[D - 2];
 }
@@ -319,15 +326,15 @@ __device__ constexpr float box_far_bound() {
   constexpr float kLn[] = {0.0f, 0.0f, 0.0f, 0.694f, 1.099f, 1.387f, 1.610f, 1.792f, 1.946f};
   return kBoxFar + kLn[D] + 0.01f;
 }
-template <int D>
+template <int D, bool LEAN = false>
 __device__ __forceinline__ void boxplus_all(const float* x, float* acc) {
   float mn = fabsf(x[0]);
 #pragma unroll
   for (int k = 1; k < D; ++k) mn = fminf(mn, fabsf(x[k]));
   if (D > 2 && __builtin_amdgcn_ballot_w64(mn < box_far_bound<D>()) == 0ull)
-    boxplus_folds<D, true>(x, acc);
+    boxplus_folds<D, true, LEAN>(x, acc);
   else
-    boxplus_folds<D, false>(x, acc);
+    boxplus_folds<D, false, LEAN>(x, acc);
 }
 
 // The check rule with a check on two neighbouring lanes (an even and an odd
@@ -387,10 +394,10 @@ __device__ __forceinline__ void boxplus_pair(const float* half, float* out) {
 // DC). Inputs x[0 .. deg). Wavefronts whose checks all have degree DC, or
 // all DC - 1, take the unrolled folds of that degree (the two degrees of the
 // spacetime window codes); mixed ones the folds with a condition per slot.
-template <int DC, bool REG>
+template <int DC, bool REG, bool LEAN = false>
 __device__ __forceinline__ void boxplus_others(const float* x, int32_t deg, float* acc) {
   if constexpr (REG) {
-    boxplus_all<DC>(x, acc);
+    boxplus_all<DC, LEAN>(x, acc);
     return;
   }
   if constexpr (DC <= 6 && DC > 2) {

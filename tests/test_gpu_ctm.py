@@ -232,3 +232,30 @@ def test_padding_checks_continuous(L, orc, name, cpt):
                             torch.from_numpy(e0).cuda(), checks_per_thread=cpt, want_fail=True)
     for k in ("z", "s", "tclr", "counts", "fail"):
         assert np.array_equal(g[k].cpu().numpy(), got[k]), k
+
+
+@pytest.mark.parametrize("bp", ["minsum", "sumproduct"])
+@pytest.mark.parametrize("name,cpts,p,t_max", [
+    ("rep:9", (1, 2, 4), 0.1, 8.0),               # fewer threads than a wavefront
+    ("toric2d:9", (1, 2, 4, 8), 0.06, 8.0),       # 81 checks: a padded tile, both copies and one
+    ("toric2d:23", (0, 1, 8), 0.05, 4.0),         # 529 checks: two per thread by default
+    ("toric3d_point:5", (0, 1, 2, 4), 0.03, 5.0),
+    ("toric3d_membrane:4", (0, 1, 2, 4), 0.04, 5.0),  # three partners per edge
+])
+def test_message_copies_and_shapes(L, orc, name, cpts, p, t_max, bp):
+    """One and two copies of the messages, packed partner words and the default shape: every
+    launch shape, with and without skipped steps, gives the oracle's bits."""
+    import torch
+    code, dc = dcode(L, name)
+    kw = dict(bp=bp, dt=0.01, t_max=t_max, seed=11)
+    e0 = (np.random.default_rng(23).random((12, code.n)) < p).astype(np.uint8)
+    o = orc.ctm_decode(code, orc.ContinuousParams(**kw), e0, shot0=5, nthreads=NTHREADS)
+    counts = np.stack([o["events"], o["moves"]], axis=1)
+    for cpt in cpts:
+        for skip in (True, False):
+            print(f"[ctm] {name} {bp} cpt={cpt} skip={skip}", flush=True)
+            g = L.decode_continuous(dc, L.ContinuousParams(skip_fixed=skip, **kw), torch.from_numpy(e0).cuda(),
+                                    shot0=5, checks_per_thread=cpt)
+            for k in ("z", "s", "tclr"):
+                assert np.array_equal(g[k].cpu().numpy(), o[k]), (k, cpt, skip)
+            assert np.array_equal(g["counts"].cpu().numpy(), counts), (cpt, skip)
