@@ -1517,10 +1517,11 @@ int device_cus(int device) {
 // round's bookkeeping and, in the tiled variant, keep messages in registers,
 // which pays once the device is full.
 //  - Full device, min-sum: 8 for (4, 2) and the tiled variant, 4 for (6, 2) and
-//    (2, 2), 2 for (4, 4), 1 for (6, 3) and the padded variants' 2 -- measured
+//    (2, 2), 1 for (4, 4) and (6, 3), the padded variants' 2 -- measured
 //    in ms at 1 / 2 / 4 / 8 checks per thread: 2D toric L = 21, 16,384 shots
 //    1.76 / 0.95 / 0.81 / 0.77; 3D point L = 12, 8,192 shots - / 29.4 / 20.1 /
-//    27.2 (8 spills); membrane L = 8, 8,192 shots - / 1.73 / 1.91; [[144,12,12]],
+//    27.2 (8 spills); membrane L = 8, 8,192 shots - / 1.73 / 1.91, L = 6 0.78 /
+//    0.85, L = 4, 16,384 shots 0.73 / 0.86 / 1.83; [[144,12,12]],
 //    131,072 shots 2.2 / 2.4 / 3.7; repetition d = 101, 131,072 shots 1.05 /
 //    0.66 / 0.56 / 0.57. At least kMinThreads threads per shot, since below
 //    that a wavefront holds many shots that wait for the slowest.
@@ -1531,7 +1532,8 @@ int device_cus(int device) {
 //  - Otherwise the fewest whose wavefronts number at most kFewWaves per SIMD
 //    (2D toric L = 16, min-sum, 1,024 shots, 4 per SIMD at one check per thread:
 //    0.112 ms against 0.182 with the tiled variant; 4,096 shots 0.232 against
-//    0.231).
+//    0.231; L = 8, 16,384 shots 0.188 with four checks per thread, shots of a
+//    part wavefront counted by their lanes, against 0.272 tiled).
 static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool tile_ok, int64_t nshots, int cus) {
   constexpr int kMaxBlock = 1024, kMinThreads = 40, kFewWaves = 4;
   auto threads = [&](int cpt) { return (c.m + cpt - 1) / cpt; };
@@ -1544,7 +1546,7 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
   } else if (tile_ok) {
     full = 8;
   } else {
-    const int most = !reg ? 4 : dc == 2 ? 4 : dv == 3 ? 1 : dv == 4 ? 2 : dc == 6 ? 4 : 8;
+    const int most = !reg ? 4 : dc == 2 ? 4 : dv >= 3 ? 1 : dc == 6 ? 4 : 8;
     const int least = dc == 2 ? 24 : kMinThreads;
     for (int a : order)
       if (usable(a) && (!full || (a <= most && threads(a) >= least))) full = a;
@@ -1552,8 +1554,11 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
   for (int i = 3; i >= 0 && !full; --i)  // no shape within 1024 threads: the largest (rejected by the caller)
     if (find_variant(dc, dv, order[i], bp, reg)) full = order[i];
   if (nshots > 0)
-    for (int a : order)
-      if (a < full && usable(a) && nshots * ((threads(a) + 63) / 64) <= (int64_t)kFewWaves * 4 * cus) return a;
+    for (int a : order) {
+      const int th = threads(a);
+      const int64_t lanes = nshots * (th < 64 ? th : (th + 63) / 64 * 64);  // shots of a part wavefront share one
+      if (a < full && usable(a) && lanes <= (int64_t)kFewWaves * 4 * 64 * cus) return a;
+    }
   return full;
 }
 
@@ -1576,11 +1581,16 @@ static bool pairs_pay(const DevCode& c, int bp, int dc, int dv, int reg, int64_t
 // of lanes in use: the shots of a block run in lockstep and wait for the
 // slowest). [[144,12,12]] (72 threads) takes 3, [[72,12,6]] (36) 7, 125 threads
 // one (3D point L = 5, min-sum, 16,384 shots: 0.56 ms as 63 x 2 x 1 against 0.81
-// as 125 x 1 x 2).
-static int built_in_spb(int nt) {
+// as 125 x 1 x 2). At least `least`: a claim of the shot queue takes 13 ns whatever
+// it claims, which bounds min-sum on small codes, so with more than 16 blocks per CU a block has
+// 96 checks or more (65,536 shots, ms with one shot per block and with two: 2D
+// toric L = 8, 64 checks, 0.85 / 0.57; 3D point L = 4, 64 checks, 0.92 / 0.73;
+// L = 5, 125 checks, 1.37 / 1.59).
+static int built_in_spb(int nt, int least) {
   int best = 1;
   double most = -1.0;
   for (int s = 1; s <= kMaxShotsPerBlock && (s == 1 || nt * s <= 256); ++s) {
+    if (s < least && nt * (s + 1) <= 256) continue;
     const double use = (double)(nt * s) / (64.0 * ((nt * s + 63) / 64)) - 0.02 * s;
     if (use > most + 1e-9) {
       most = use;
@@ -1648,10 +1658,16 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
   }
   const int vpt = (c.n + nt - 1) / nt;
   if (spb <= 0 && tile_ok && cpt == 8 && nt * 8 == c.m) {
-    // blocks near 128 threads with wavefronts at least 80% full (measured:
-    // 128 threads best at L = 8 and 32, 216 at L = 24, 64-128 at L = 16)
+    // one wavefront, whose barriers cost nothing, if two shots or more fill 80%
+    // of it (65,536 shots, ms with one wavefront and with about 128 threads: L = 8
+    // 0.463 / 0.477, L = 12 0.85 / 1.01, L = 16 1.25 / 1.36); else blocks near 128
+    // threads with wavefronts at least 80% full (128 threads best at L = 32, 216 at
+    // L = 24)
     int best = 0, gap = 0;
-    for (int s = 1; nt * s <= kTileMaxThreads; ++s) {
+    const int one = 64 / nt;  // shots of one wavefront
+    const bool single = one >= 2 && 5 * nt * one >= 4 * 64;
+    if (single) best = one;
+    for (int s = 1; !single && nt * s <= kTileMaxThreads; ++s) {
       const int th = nt * s, waves = (th + 63) / 64;
       if (5 * th < 4 * 64 * waves) continue;
       const int d = th > 128 ? th - 128 : 128 - th;
@@ -1663,7 +1679,13 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
     spb = best > 0 ? best : 1;
   }
   if (spb <= 0) {
-    spb = built_in_spb(nt);
+    int64_t least = 1;
+    if ((bp == 0 || dc == 2) && lpc == 1) {
+      least = (96 + nt * cpt - 1) / (nt * cpt);
+      const int64_t room = nshots / (16 * (int64_t)device_cus(device));  // 0 shots: a full device
+      if (nshots > 0 && least > room) least = room > 1 ? room : 1;
+    }
+    spb = built_in_spb(nt, (int)least);
     // as many as the LDS holds (and not more than there are)
     const size_t gb1 = group_bytes_for(dc, (nt / lpc * cpt + 63) / 64 * 64, c.n, c.m, seq);
     while (spb > 1 && (kCtrlWords * 4 + gb1 * (size_t)spb > (size_t)lds_max || (nshots > 0 && spb > nshots))) --spb;

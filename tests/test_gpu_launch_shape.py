@@ -80,3 +80,21 @@ def test_two_threads_per_check(L, orc, name, cpt):
                     assert np.array_equal(g[key].cpu().numpy(), o[key]), (spb, conflict, q, key)
                 assert np.array_equal(g["L"].cpu().numpy().view(np.uint32), o["L"].view(np.uint32)), (spb, conflict, q)
                 assert np.array_equal(g["fail"].cpu().numpy(), orc.logical_failure(spec, e0, o["z"]))
+
+
+@pytest.mark.parametrize("name", ["rep:51", "toric2d:4", "toric2d:8", "toric2d:12", "toric2d:16",
+                                  "toric3d_point:4", "toric3d_membrane:4"])
+def test_small_codes_in_large_batches(L, name):
+    """Min-sum on small codes: several shots per block and part wavefronts by the built-in
+    rule, on either side of the batch sizes where it changes, against one shot per block."""
+    import torch
+    spec = codes.by_name(name)
+    dc = L.Code(spec, 0)
+    P = L.DecodeParams(bp="minsum", q=0.125 if "membrane" in name else 0.05, rounds=6, seed=5)
+    e0 = L.sample_noise(dc, 0.05, 3, 0, 40000)
+    ref = L.decode_rounds(dc, P, e0, cfg={"checks_per_thread": 1, "shots_per_block": 1}, want_fail=True)
+    for S in (8191, 8192, 16384, 32769, 40000):
+        print(f"[shape] {name} shots={S}", flush=True)
+        g = L.decode_rounds(dc, P, e0[:S].contiguous(), want_fail=True)
+        for k in ("z", "s", "tclr", "fail"):
+            assert torch.equal(g[k], ref[k][:S]), (S, k)
