@@ -329,7 +329,7 @@ constexpr int kFusedMaxWords = 4;  // logicals folded in LDS by the fused failur
 
 template <bool B>
 struct BoolTag {
-  static constexpr bool value = B;
+  constexpr operator bool() const { return B; }
 };
 
 __device__ __forceinline__ GroupJob dead_job() {
@@ -668,7 +668,7 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
           for (int j = 0; j < DC; ++j)
             if (tile_partner(k, j) >= 0) io[TILE ? k : 0][j] = msg[msg_word<DC>(tc + k * ntc, j)];
       }
-      // With CMP, a sweep may also compare each new message with the one
+      // With CMP, a sweep also compares each new message with the one
       // it replaces; comparing costs half a sweep's worth of extra VALU per
       // check, so it is done every eighth sweep and at the last of the
       // round, and a fixed point is found at most seven sweeps late (those
@@ -677,148 +677,178 @@ __device__ void run_units(const DevCode& c, const KParams& kp, const UnitCtx& u,
       // is cleared only after every thread has read it. A shot's first
       // sweep (m_{v->c} = 0 rather than pi + sum m_{c->v}) is another map
       // and never counts as a fixed point.
-      auto sweeps = [&](auto cmp_tag) {
-        constexpr bool CMP_ON = decltype(cmp_tag)::value;
-        int32_t ncmp = 0;  // compared sweeps so far in this round
-        for (int32_t it = it0; it < kp.iters; ++it) {
-          const bool CMP = CMP_ON && ((it & 7) == 7 || it == kp.iters - 1);
-          const int32_t f = ncmp & 1;
-          const bool first = fresh;
-          float x[CPT][HD];
-          if (sweep) {
-            if (!REG && fresh) {
+      int32_t ncmp = 0;  // compared sweeps so far in this round
+      auto one_sweep = [&](auto cmp) {
+        const bool CMP = cmp;
+        const int32_t f = ncmp & 1;
+        const bool first = fresh;
+        float x[CPT][HD];
+        if (sweep) {
+          if (!REG && fresh) {
 #pragma unroll
-              for (int k = 0; k < CPT; ++k)
+            for (int k = 0; k < CPT; ++k)
 #pragma unroll
-                for (int j = 0; j < HD; ++j) x[k][j] = (j >= deg[k]) ? __builtin_inff() : 0.0f;
-            } else {
-#pragma unroll
-              for (int k = 0; k < CPT; ++k) {
-#pragma unroll
-                for (int j = 0; j < HD; ++j) {
-                  // (inside a tile the input is formed after the barrier,
-                  // from a register)
-                  if (TILE && tile_partner(k, j) >= 0) continue;
-                  float acc = pi;
-#pragma unroll
-                  for (int p = 0; p < DV - 1; ++p) acc = acc + msg[pidx[k][j][p]];
-                  // min-sum on qubits of degree 2 (exact variants, run only when
-                  // alpha < 1 and |pi| / (1 - alpha) < CLAMP): |m_{v->c}| stays
-                  // below |pi| / (1 - alpha), so the clamp cannot bind
-                  if (!(BP == 0 && REG && DV == 2)) acc = __builtin_amdgcn_fmed3f(acc, -C, C);
-                  if (!REG && j >= deg[k]) acc = __builtin_inff();
-                  x[k][j] = acc;
-                }
-              }
-            }
-          }
-          __syncthreads();
-          if (CMP) {
-            if (member && t == 0) gw[f ? kGwChg0 : kGwChg1] = 0;
-            if (tid == 0) ctrl[f ? kCtrlChg0 : kCtrlChg1] = 0;
-          }
-          uint32_t diff = 0u;
-          if (sweep) {
-            // Inside a tile the checks' outputs replace the last sweep's in
-            // place: when check k runs, the inputs that its outputs feed in
-            // a later check are formed first (xpre), from the old outputs;
-            // the inputs it takes from an earlier check were formed there.
-            float xpre[TILE ? CPT : 1][DC];
+              for (int j = 0; j < HD; ++j) x[k][j] = (j >= deg[k]) ? __builtin_inff() : 0.0f;
+          } else {
 #pragma unroll
             for (int k = 0; k < CPT; ++k) {
-              if (TILE) {
-#pragma unroll
-                for (int j = 0; j < DC; ++j) {
-                  const int tp = tile_partner(k, j);
-                  if (tp < 0) continue;
-                  x[k][j] = (tp >> 2) < k ? xpre[TILE ? k : 0][j] : pi + io[TILE ? tp >> 2 : 0][tp & 3];
-                }
-#pragma unroll
-                for (int j = 0; j < DC; ++j) {
-                  const int tp = tile_partner(k, j);
-                  if (tp >= 0 && (tp >> 2) > k) xpre[TILE ? tp >> 2 : 0][tp & 3] = pi + io[TILE ? k : 0][j];
-                }
-              }
-              const uint32_t sigma_neg = ((sb >> k) ^ (uint32_t)(REG ? DC : deg[k])) & 1u;
-              float out[HD];
-              if constexpr (BP == 0) {
-                // normalised min-sum: alpha * (smallest other |m|) with the
-                // sign product. No input is -0 (pi + messages with pi != -0,
-                // or +0 on a fresh sweep), so the sign bit is sg(). The sign
-                // product of all inputs goes into the scale (alpha * min
-                // rounds the same for either sign); each output then removes
-                // its own input's sign with one bit operation.
-                uint32_t par = sigma_neg << 31;
-#pragma unroll
-                for (int j = 0; j + 1 < DC; j += 2)
-                  par = xor3(par, __float_as_uint(x[k][j]), __float_as_uint(x[k][j + 1]));
-                if (DC & 1) par ^= __float_as_uint(x[k][DC - 1]);
-                const float alpha_s = __uint_as_float(__float_as_uint(kp.alpha) ^ (par & 0x80000000u));
-                float ex[DC];  // smallest |m| over the other inputs
-                min_others<DC>(x[k], ex);
-#pragma unroll
-                for (int j = 0; j < DC; ++j) {
-                  // With degree >= 2 there is an input to take the minimum of,
-                  // so |v| <= alpha * clamp <= clamp (the resident min-sum path
-                  // runs only with alpha <= 1) and the output clamp cannot bind;
-                  // a degree-1 check of an irregular code has an empty minimum
-                  // (+inf) and is clamped.
-                  float v = alpha_s * ex[j];
-                  if (!REG) v = __builtin_amdgcn_fmed3f(v, -C, C);
-                  out[j] = __uint_as_float(__float_as_uint(v) ^ (__float_as_uint(x[k][j]) & 0x80000000u));
-                }
-              } else {
-                // sum-product: box-plus of the other inputs (prefix/suffix folds)
-                float acc[HD];
-                if constexpr (LPC == 2)
-                  boxplus_pair<DC>(x[k], acc);
-                else
-                  boxplus_others<DC, REG>(x[k], deg[k], acc);
-#pragma unroll
-                for (int j = 0; j < HD; ++j) out[j] = __builtin_amdgcn_fmed3f(sigma_neg ? -acc[j] : acc[j], -C, C);
-              }
-              float* mk = msg + msg_word<DC>(tc + k * ntc, 0);
-              if (CMP) {  // padding checks and the padding slots of irregular checks are never read
-                uint32_t dk = 0u;
-#pragma unroll
-                for (int j = 0; j < HD; ++j) {
-                  const float old =
-                      (TILE && tile_partner(k, j) >= 0) ? io[TILE ? k : 0][j] : mk[out_slot(j) * kSlotStride];
-                  if (REG || j < deg[k]) dk |= __float_as_uint(old) ^ __float_as_uint(out[j]);
-                }
-                diff |= ((vmask >> k) & 1u) ? dk : 0u;
-              }
 #pragma unroll
               for (int j = 0; j < HD; ++j) {
-                if (TILE && tile_partner(k, j) >= 0)
-                  io[TILE ? k : 0][j] = out[j];  // read from a register within the tile
-                else
-                  mk[out_slot(j) * kSlotStride] = out[j];
+                // (inside a tile the input is formed after the barrier,
+                // from a register)
+                if (TILE && tile_partner(k, j) >= 0) continue;
+                float acc = pi;
+#pragma unroll
+                for (int p = 0; p < DV - 1; ++p) acc = acc + msg[pidx[k][j][p]];
+                // min-sum on qubits of degree 2 (exact variants, run only when
+                // alpha < 1 and |pi| / (1 - alpha) < CLAMP): |m_{v->c}| stays
+                // below |pi| / (1 - alpha), so the clamp cannot bind
+                if (!(BP == 0 && REG && DV == 2)) acc = __builtin_amdgcn_fmed3f(acc, -C, C);
+                if (!REG && j >= deg[k]) acc = __builtin_inff();
+                x[k][j] = acc;
               }
             }
           }
-          swept = swept || sweep;
-          if (CMP && sweep && (diff || first)) {
-            gw[f ? kGwChg1 : kGwChg0] = 1;
-            ctrl[f ? kCtrlChg1 : kCtrlChg0] = 1;
-          }
-          fresh = false;
-          __syncthreads();
-          nsweeps += (sweep && nsweeps != 0x7fffffff) ? 1 : 0;  // saturating
-          if (CMP) {
-            ++ncmp;
-            if (sweep && gw[f ? kGwChg1 : kGwChg0] == 0) {
-              sweep = false;
-              conv = true;
+        }
+        __syncthreads();
+        if (CMP) {
+          if (member && t == 0) gw[f ? kGwChg0 : kGwChg1] = 0;
+          if (tid == 0) ctrl[f ? kCtrlChg0 : kCtrlChg1] = 0;
+        }
+        uint32_t diff = 0u;
+        if (sweep) {
+          // Inside a tile the checks' outputs replace the last sweep's in
+          // place: when check k runs, the inputs that its outputs feed in
+          // a later check are formed first (xpre), from the old outputs;
+          // the inputs it takes from an earlier check were formed there.
+          float xpre[TILE ? CPT : 1][DC];
+#pragma unroll
+          for (int k = 0; k < CPT; ++k) {
+            if (TILE) {
+#pragma unroll
+              for (int j = 0; j < DC; ++j) {
+                const int tp = tile_partner(k, j);
+                if (tp < 0) continue;
+                x[k][j] = (tp >> 2) < k ? xpre[TILE ? k : 0][j] : pi + io[TILE ? tp >> 2 : 0][tp & 3];
+              }
+#pragma unroll
+              for (int j = 0; j < DC; ++j) {
+                const int tp = tile_partner(k, j);
+                if (tp >= 0 && (tp >> 2) > k) xpre[TILE ? tp >> 2 : 0][tp & 3] = pi + io[TILE ? k : 0][j];
+              }
             }
-            if (ctrl[f ? kCtrlChg1 : kCtrlChg0] == 0) break;  // no group changed
+            const uint32_t sigma_neg = ((sb >> k) ^ (uint32_t)(REG ? DC : deg[k])) & 1u;
+            float out[HD];
+            if constexpr (BP == 0) {
+              // normalised min-sum: alpha * (smallest other |m|) with the
+              // sign product. No input is -0 (pi + messages with pi != -0,
+              // or +0 on a fresh sweep), so the sign bit is sg(). The sign
+              // product of all inputs goes into the scale (alpha * min
+              // rounds the same for either sign); each output then removes
+              // its own input's sign with one bit operation.
+              uint32_t par = sigma_neg << 31;
+#pragma unroll
+              for (int j = 0; j + 1 < DC; j += 2)
+                par = xor3(par, __float_as_uint(x[k][j]), __float_as_uint(x[k][j + 1]));
+              if (DC & 1) par ^= __float_as_uint(x[k][DC - 1]);
+              const float alpha_s = __uint_as_float(__float_as_uint(kp.alpha) ^ (par & 0x80000000u));
+              float ex[DC];  // smallest |m| over the other inputs
+              min_others<DC>(x[k], ex);
+#pragma unroll
+              for (int j = 0; j < DC; ++j) {
+                // With degree >= 2 there is an input to take the minimum of,
+                // so |v| <= alpha * clamp <= clamp (the resident min-sum path
+                // runs only with alpha <= 1) and the output clamp cannot bind;
+                // a degree-1 check of an irregular code has an empty minimum
+                // (+inf) and is clamped.
+                float v = alpha_s * ex[j];
+                if (!REG) v = __builtin_amdgcn_fmed3f(v, -C, C);
+                out[j] = __uint_as_float(__float_as_uint(v) ^ (__float_as_uint(x[k][j]) & 0x80000000u));
+              }
+            } else {
+              // sum-product: box-plus of the other inputs (prefix/suffix folds)
+              float acc[HD];
+              if constexpr (LPC == 2)
+                boxplus_pair<DC>(x[k], acc);
+              else
+                boxplus_others<DC, REG>(x[k], deg[k], acc);
+#pragma unroll
+              for (int j = 0; j < HD; ++j) out[j] = __builtin_amdgcn_fmed3f(sigma_neg ? -acc[j] : acc[j], -C, C);
+            }
+            float* mk = msg + msg_word<DC>(tc + k * ntc, 0);
+            if (CMP) {  // padding checks and the padding slots of irregular checks are never read
+              uint32_t dk = 0u;
+#pragma unroll
+              for (int j = 0; j < HD; ++j) {
+                const float old =
+                    (TILE && tile_partner(k, j) >= 0) ? io[TILE ? k : 0][j] : mk[out_slot(j) * kSlotStride];
+                if (REG || j < deg[k]) dk |= __float_as_uint(old) ^ __float_as_uint(out[j]);
+              }
+              diff |= ((vmask >> k) & 1u) ? dk : 0u;
+            }
+#pragma unroll
+            for (int j = 0; j < HD; ++j) {
+              if (TILE && tile_partner(k, j) >= 0)
+                io[TILE ? k : 0][j] = out[j];  // read from a register within the tile
+              else
+                mk[out_slot(j) * kSlotStride] = out[j];
+            }
           }
         }
+        swept = swept || sweep;
+        if (CMP && sweep && (diff || first)) {
+          gw[f ? kGwChg1 : kGwChg0] = 1;
+          ctrl[f ? kCtrlChg1 : kCtrlChg0] = 1;
+        }
+        fresh = false;
+        __syncthreads();
       };
-      if (kp.skip)
-        sweeps(BoolTag<true>());
-      else
-        sweeps(BoolTag<false>());
+      auto compared = [&]() {  // after a compared sweep; false: no group changed
+        const int32_t f = ncmp & 1;
+        ++ncmp;
+        if (sweep && gw[f ? kGwChg1 : kGwChg0] == 0) {
+          sweep = false;
+          conv = true;
+        }
+        return ctrl[f ? kCtrlChg1 : kCtrlChg0] != 0;
+      };
+      auto count = [&](int32_t n) {
+        if (sweep) nsweeps += n < 0x7fffffff - nsweeps ? n : 0x7fffffff - nsweeps;  // saturating
+      };
+      // The sweeps between two compared ones have a loop of their own that
+      // holds nothing else: no branch on the compare after every check, no
+      // registers copied at its turn (min-sum, 8,192 shots, 24 rounds, ms with
+      // the branches and without: 2D toric L = 8 0.135 / 0.114, 3D point L = 12
+      // 7.40 / 6.93, [[144,12,12]] 0.34 / 0.30). With many edges per thread
+      // the checks of a sweep without branches between them run out of registers
+      // (tiled 2D L = 32, 65,536 shots: 108 spills, 6.38 ms against 5.53);
+      // there one sweep serves for both and branches.
+      constexpr bool kMany = TILE || (CPT == 8 && (DC != 4 || BP != 0)) || (CPT == 4 && DV > 2);
+      const int32_t last = kp.iters - 1;
+      int32_t it = it0;
+      if (!kp.skip) {
+        count(kp.iters > it ? kp.iters - it : 0);
+#pragma unroll 1
+        for (; it < kp.iters; ++it) one_sweep(BoolTag<false>());
+      } else if constexpr (kMany) {
+#pragma unroll 1
+        for (; it < kp.iters; ++it) {
+          const bool cmp = (it & 7) == 7 || it == last;
+          count(1);
+          one_sweep(cmp);
+          if (cmp && !compared()) break;
+        }
+      } else {
+        while (it < kp.iters) {
+          const int32_t stop = (it | 7) < last ? (it | 7) : last;  // the next compared sweep
+          count(stop - it + 1);
+#pragma unroll 1
+          for (; it < stop; ++it) one_sweep(BoolTag<false>());
+          one_sweep(BoolTag<true>());
+          ++it;
+          if (!compared()) break;
+        }
+      }
       if (TILE) {
         // the tile's inner messages back to LDS, for the feedback and the
         // next round's sweeps (anyw is the same in every thread of the block)
