@@ -1549,21 +1549,22 @@ int device_cus(int device) {
 //  - Full device, min-sum: 8 for (4, 2) and the tiled variant, 4 for (6, 2) and
 //    (2, 2), 1 for (4, 4) and (6, 3), the padded variants' 2 -- measured
 //    in ms at 1 / 2 / 4 / 8 checks per thread: 2D toric L = 21, 16,384 shots
-//    1.76 / 0.95 / 0.81 / 0.77; 3D point L = 12, 8,192 shots - / 29.4 / 20.1 /
-//    27.2 (8 spills); membrane L = 8, 8,192 shots - / 1.73 / 1.91, L = 6 0.78 /
-//    0.85, L = 4, 16,384 shots 0.73 / 0.86 / 1.83; [[144,12,12]],
-//    131,072 shots 2.2 / 2.4 / 3.7; repetition d = 101, 131,072 shots 1.05 /
-//    0.66 / 0.56 / 0.57. At least kMinThreads threads per shot, since below
+//    1.54 / 0.91 / 0.82 / 0.82; 3D point L = 12, 8,192 shots - / 25.1 / 18.0 /
+//    19.3 (36 spills); membrane L = 8, 8,192 shots - / 1.64 / 1.92, L = 6 0.66 /
+//    0.72 / 1.04, L = 4, 16,384 shots 0.61 / 0.73 / 1.85; [[144,12,12]],
+//    131,072 shots 1.71 / 1.94 / 3.75; repetition d = 101, 131,072 shots 1.56 /
+//    0.70 / 0.71 / 0.86. At least kMinThreads threads per shot, since below
 //    that a wavefront holds many shots that wait for the slowest.
 //  - Full device, sum-product: the fewest with at most 640 threads per shot (2D
-//    toric L = 32, 16,384 shots 26.9 / 23.3 / 25.7 / 30.9; 3D point L = 12, 4,096
-//    shots - / 37.4 / 33.3 / 39.6); checks of degree 2 have no box-plus step
+//    toric L = 32, 16,384 shots 23.8 / 21.9 / 23.4 / 30.5; 3D point L = 12, 4,096
+//    shots - / 36.9 / 34.0 / 39.4); checks of degree 2 have no box-plus step
 //    and follow the min-sum rule.
 //  - Otherwise the fewest whose wavefronts number at most kFewWaves per SIMD
 //    (2D toric L = 16, min-sum, 1,024 shots, 4 per SIMD at one check per thread:
-//    0.112 ms against 0.182 with the tiled variant; 4,096 shots 0.232 against
-//    0.231; L = 8, 16,384 shots 0.188 with four checks per thread, shots of a
-//    part wavefront counted by their lanes, against 0.272 tiled).
+//    0.090 ms against 0.205 with the tiled variant; 4,096 shots, 4 per SIMD at
+//    four, 0.161 against 0.230; L = 8, 16,384 shots 0.167 with four checks per
+//    thread, shots of a part wavefront counted by their lanes, against 0.259
+//    tiled).
 static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool tile_ok, int64_t nshots, int cus) {
   constexpr int kMaxBlock = 1024, kMinThreads = 40, kFewWaves = 4;
   auto threads = [&](int cpt) { return (c.m + cpt - 1) / cpt; };
