@@ -318,7 +318,9 @@ laim_status laim_resident_variant(const laim_code* code, const laim_decode_param
  * threads per shot, in blocks of at most 256 threads (or one shot) with their
  * wavefronts full. Smaller batches take the fewest checks per thread whose
  * wavefronts the device holds at once. A field given as 0 in cfg is chosen by
- * the same rule. */
+ * the same rule, among the shapes whose block (threads_per_shot *
+ * shots_per_block) has at most 1024 threads; whether it runs does not depend on
+ * the batch size. */
 laim_status laim_set_resident_cfg(laim_code* code, int32_t bp, const laim_resident_cfg* cfg);
 /* The launch shape that would be used for a batch that fills the device (after
  * the built-in rule). */

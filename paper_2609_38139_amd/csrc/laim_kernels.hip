@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "device_math.h"
 #include "laim_internal.h"
 
@@ -1565,10 +1567,17 @@ int device_cus(int device) {
 //    four, 0.161 against 0.230; L = 8, 16,384 shots 0.167 with four checks per
 //    thread, shots of a part wavefront counted by their lanes, against 0.259
 //    tiled).
-static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool tile_ok, int64_t nshots, int cus) {
-  constexpr int kMaxBlock = 1024, kMinThreads = 40, kFewWaves = 4;
+// spb: the caller's shots per block, or 0. Only shapes whose block then has at
+// most kMaxBlock threads are taken, for the full device and for fewer shots
+// alike, so that whether a shape is accepted does not depend on nshots.
+constexpr int kMaxBlock = 1024;
+static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool tile_ok, int64_t nshots, int cus,
+                        int spb) {
+  constexpr int kMinThreads = 40, kFewWaves = 4;
   auto threads = [&](int cpt) { return (c.m + cpt - 1) / cpt; };
-  auto usable = [&](int cpt) { return threads(cpt) <= kMaxBlock && find_variant(dc, dv, cpt, bp, reg); };
+  auto usable = [&](int cpt) {
+    return threads(cpt) * std::max(spb, 1) <= kMaxBlock && find_variant(dc, dv, cpt, bp, reg);
+  };
   static const int order[] = {1, 2, 4, 8};
   int full = 0;
   if (bp != 0 && dc > 2) {
@@ -1582,7 +1591,7 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
     for (int a : order)
       if (usable(a) && (!full || (a <= most && threads(a) >= least))) full = a;
   }
-  for (int i = 3; i >= 0 && !full; --i)  // no shape within 1024 threads: the largest (rejected by the caller)
+  for (int i = 3; i >= 0 && !full; --i)  // none of those: the most checks per thread (the caller checks the block)
     if (find_variant(dc, dv, order[i], bp, reg)) full = order[i];
   if (nshots > 0)
     for (int a : order) {
@@ -1602,8 +1611,9 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
 // 0.99 and 1.11) -- and on (6, 3) codes always: a few shots that never clear
 // set the end of a launch of their short shots ([[144,12,12]], 65,536 shots, p =
 // 0.03: 5.29 and 3.70; [[72,12,6]] 0.85 and 0.78).
-static bool pairs_pay(const DevCode& c, int bp, int dc, int dv, int reg, int64_t nshots, int cus) {
-  if (bp != 1 || 2 * c.m > 900 || !find_variant(dc, dv, 1, bp, reg, 0, 2)) return false;
+static bool pairs_pay(const DevCode& c, int bp, int dc, int dv, int reg, int64_t nshots, int cus, int spb) {
+  if (bp != 1 || 2 * c.m > 900 || 2 * c.m * std::max(spb, 1) > kMaxBlock || !find_variant(dc, dv, 1, bp, reg, 0, 2))
+    return false;
   return dv == 3 || (nshots > 0 && nshots * ((c.m + 63) / 64) <= (int64_t)8 * 4 * cus);
 }
 
@@ -1646,15 +1656,15 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
     lds_max = 64 * 1024;
   int cpt = want ? want->checks_per_thread : 0;
   int nt = want ? want->threads_per_shot : 0;
-  int spb = want ? want->shots_per_block : 0;
+  int spb = std::min(want ? want->shots_per_block : 0, kMaxShotsPerBlock);
   // min-sum on the 2D toric layout: the tiled variant, on a full device faster
   // than the other shapes at every L measured (8 to 64)
   const bool tile_ok = c.tile_chk && bp == 0 && dc == 4 && dv == 2 && reg && !seq;
   int lpc = 1;
   if (cpt <= 0 && nt <= 0) {
     const int cus = device_cus(device);
-    cpt = built_in_cpt(c, bp, dc, dv, reg, tile_ok, nshots, cus);
-    if (pairs_pay(c, bp, dc, dv, reg, nshots, cus)) {
+    cpt = built_in_cpt(c, bp, dc, dv, reg, tile_ok, nshots, cus, spb);
+    if (pairs_pay(c, bp, dc, dv, reg, nshots, cus, spb)) {
       cpt = 1;
       lpc = 2;
     }
@@ -1722,8 +1732,8 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
     while (spb > 1 && (kCtrlWords * 4 + gb1 * (size_t)spb > (size_t)lds_max || (nshots > 0 && spb > nshots))) --spb;
   }
   if (spb > kMaxShotsPerBlock) spb = kMaxShotsPerBlock;
-  if (nt * spb > 1024) {
-    set_error("block of %d threads exceeds 1024", nt * spb);
+  if (nt * spb > kMaxBlock) {
+    set_error("block of %d threads exceeds %d", nt * spb, kMaxBlock);
     return false;
   }
   const int mpad = (nt / lpc * cpt + 63) / 64 * 64;
