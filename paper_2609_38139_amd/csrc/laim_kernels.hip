@@ -1548,8 +1548,11 @@ int device_cus(int device) {
 // checks run one after another); more of them amortise the barriers, the
 // round's bookkeeping and, in the tiled variant, keep messages in registers,
 // which pays once the device is full.
-//  - Full device, min-sum: 8 for (4, 2) and the tiled variant, 4 for (6, 2) and
-//    (2, 2), 1 for (4, 4) and (6, 3), the padded variants' 2 -- measured
+//  - Full device, min-sum: 8 for (4, 2) and the tiled variant, 4 for (6, 2),
+//    padded or not, and (2, 2), 1 for (4, 4) and (6, 3), for padded (8, 4) 1 up to
+//    256 checks and 2 above (4 spills most of its 96 partner addresses: mixed
+//    degrees 3 to 8, 8,192 shots, ms at 1 / 2 / 4, 200 checks 0.72 / 1.02 / 4.79,
+//    448 1.32 / 1.26 / 4.72, 900 3.69 / 3.02 / 10.3) -- measured
 //    in ms at 1 / 2 / 4 / 8 checks per thread: 2D toric L = 21, 16,384 shots
 //    1.54 / 0.91 / 0.82 / 0.82; 3D point L = 12, 8,192 shots - / 25.1 / 18.0 /
 //    19.3 (36 spills); membrane L = 8, 8,192 shots - / 1.64 / 1.92, L = 6 0.66 /
@@ -1586,7 +1589,8 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
   } else if (tile_ok) {
     full = 8;
   } else {
-    const int most = !reg ? 4 : dc == 2 ? 4 : dv >= 3 ? 1 : dc == 6 ? 4 : 8;
+    const bool wide_pad = !reg && dv == 4;
+    const int most = wide_pad ? (c.m > 256 ? 2 : 1) : !reg || dc == 2 ? 4 : dv >= 3 ? 1 : dc == 6 ? 4 : 8;
     const int least = dc == 2 ? 24 : kMinThreads;
     for (int a : order)
       if (usable(a) && (!full || (a <= most && threads(a) >= least))) full = a;

@@ -1,5 +1,5 @@
-"""The launch-shape rule on the CPU: a shape that gives the shots per block
-alone is answered the same way at every batch size."""
+"""The launch-shape rule on the CPU: which shapes it accepts, and the lines where
+its choice changes."""
 import os
 import subprocess
 
@@ -32,6 +32,9 @@ CHECKS = (16, 36, 64, 72, 100, 125, 128, 169, 216, 256, 257, 288, 432, 441, 448,
           1000, 1024)
 
 
+BATCHES = (0, 1, 40, 256, 1024, 4096, 65536, 2**31 - 1)
+
+
 def test_a_shape_with_shots_per_block_alone_is_accepted_at_every_batch_size(shapes):
     rows = []
     for dc, dv, regular, lattice, per in FAMILIES:
@@ -41,19 +44,31 @@ def test_a_shape_with_shots_per_block_alone_is_accepted_at_every_batch_size(shap
             for bp in (0, 1):
                 for seq in (0, 1):
                     for spb in (1, 2, 3, 4, 5, 8, 13, 16, 31, 40):
-                        rows.append((m, m * per, dc, dv, regular, lattice, bp, seq, spb))
+                        rows += [(m, m * per, dc, dv, regular, lattice, bp, seq, spb, n) for n in BATCHES]
     got = shapes(rows)
     assert len(got) == len(rows)
     accepted = 0
-    for row, out in zip(rows, got):
-        m, spb = row[0], min(row[8], 31)
-        full, per_batch = out[0], [out[1 + 4 * i:5 + 4 * i] for i in range((len(out) - 1) // 4)]
-        oks = {p[0] for p in per_batch}
-        assert len(oks) == 1, (row, out)  # the answer does not depend on the batch
-        if full:  # and is yes wherever the block written out in full runs
-            assert oks == {1}, (row, out)
-        for ok, nt, cpt, lanes in per_batch:
+    for i in range(0, len(rows), len(BATCHES)):
+        row, outs = rows[i], got[i:i + len(BATCHES)]
+        oks = {o[1] for o in outs}
+        assert len(oks) == 1, (row, outs)  # the answer does not depend on the batch
+        if outs[0][0]:  # and is yes wherever the block written out in full runs
+            assert oks == {1}, (row, outs)
+        for _, ok, nt, cpt, lanes, spb in outs:
             if ok:
                 accepted += 1
-                assert nt * spb <= 1024 and nt // lanes * cpt >= m, (row, out)
+                assert spb == min(row[8], 31) and nt * spb <= 1024 and nt // lanes * cpt >= row[0], (row, outs)
     assert accepted > 10000
+
+
+def shape_of(shapes, m, dc, dv, regular, bp, nshots, per=2):
+    """(threads, checks per thread, lanes per check, shots per block) of the rule's own choice."""
+    (_, ok, *shape), = shapes([(m, m * per, dc, dv, regular, 0, bp, 0, 0, nshots)])
+    assert ok
+    return tuple(shape)
+
+
+@pytest.mark.parametrize("nshots", [0, 8192, 65536])
+def test_padded_degree_8_min_sum_never_takes_four_checks_per_thread(shapes, nshots):
+    for m in (100, 200, 256, 257, 448, 600, 900, 1024):
+        assert shape_of(shapes, m, 8, 4, 0, 0, nshots)[1] == (1 if m <= 256 else 2), m
