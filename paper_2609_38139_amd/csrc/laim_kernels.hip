@@ -1548,18 +1548,28 @@ int device_cus(int device) {
 // checks run one after another); more of them amortise the barriers, the
 // round's bookkeeping and, in the tiled variant, keep messages in registers,
 // which pays once the device is full.
-//  - Full device, min-sum: 8 for (4, 2) and the tiled variant, 4 for (6, 2),
-//    padded or not, and (2, 2), 1 for (4, 4) and (6, 3), for padded (8, 4) 1 up to
-//    256 checks and 2 above (4 spills most of its 96 partner addresses: mixed
-//    degrees 3 to 8, 8,192 shots, ms at 1 / 2 / 4, 200 checks 0.72 / 1.02 / 4.79,
-//    448 1.32 / 1.26 / 4.72, 900 3.69 / 3.02 / 10.3) -- measured
-//    in ms at 1 / 2 / 4 / 8 checks per thread: 2D toric L = 21, 16,384 shots
-//    1.54 / 0.91 / 0.82 / 0.82; 3D point L = 12, 8,192 shots - / 25.1 / 18.0 /
-//    19.3 (36 spills); membrane L = 8, 8,192 shots - / 1.64 / 1.92, L = 6 0.66 /
-//    0.72 / 1.04, L = 4, 16,384 shots 0.61 / 0.73 / 1.85; [[144,12,12]],
-//    131,072 shots 1.71 / 1.94 / 3.75; repetition d = 101, 131,072 shots 1.56 /
-//    0.70 / 0.71 / 0.86. At least kMinThreads threads per shot, since below
-//    that a wavefront holds many shots that wait for the slowest.
+//  - Full device, min-sum, by degrees and the number of checks (ms at 1 / 2 / 4 /
+//    8 checks per thread):
+//    (4, 2): up to 8 with at least 40 threads per shot, below which a wavefront
+//    holds many shots that wait for the slowest (2D toric L = 21, 16,384 shots 1.54
+//    / 0.91 / 0.82 / 0.82); the tiled variant always 8.
+//    (2, 2): up to 4 with at least 24 threads (repetition d = 101, 131,072 shots
+//    1.56 / 0.70 / 0.71 / 0.86).
+//    (6, 2), padded or not: 2 with 40 threads, 4 with 100 (3D point, 32,768 shots,
+//    p = 0.02: L = 6, 216 checks, - / 1.37 / 1.33, of 8,192 shots 0.56 / 0.67; L = 7,
+//    343 checks, - / 2.78 / 3.03; L = 8, 512 checks, 6.69 / 4.46 / 3.76; L = 12, 8,192
+//    shots - / 25.1 / 18.0 / 19.3, 36 spills).
+//    (6, 3): 1 up to 256 checks, 2 above (8,192 shots at p = 0.006, 8 rounds: 252
+//    checks 0.18 / 0.18, 324 0.37 / 0.25, 378 0.38 / 0.24, 900 1.29 / 0.90; at p =
+//    0.03, 32 rounds: 252 0.49 / 0.57, 324 0.71 / 0.68, 378 0.81 / 0.73, 900 2.33 / 1.75;
+//    [[144,12,12]], 131,072 shots 1.71 / 1.94 / 3.75).
+//    (4, 4): 1, but 2 for 257 to 512 checks if that takes half the wavefronts
+//    (membrane, 32,768 shots, p = 0.03 and 0.006: L = 5, 375 checks, 0.94 / 0.74 and
+//    0.58 / 0.43; L = 4, 192 checks, 0.64 / 0.72 and 0.41 / 0.42; L = 6, 648 checks in
+//    11 or 6 wavefronts, 2.02 / 2.21 / 2.37 and 1.15 / 1.22 / 1.05).
+//    Padded (8, 4): 1 up to 256 checks, 2 above; 4 spills most of its 96 partner
+//    addresses (mixed degrees 3 to 8, 8,192 shots: 200 checks 0.72 / 1.02 / 4.79,
+//    448 1.32 / 1.26 / 4.72, 900 3.69 / 3.02 / 10.3).
 //  - Full device, sum-product: the fewest with at most 640 threads per shot (2D
 //    toric L = 32, 16,384 shots 23.8 / 21.9 / 23.4 / 30.5; 3D point L = 12, 4,096
 //    shots - / 36.9 / 34.0 / 39.4); checks of degree 2 have no box-plus step
@@ -1576,7 +1586,7 @@ int device_cus(int device) {
 constexpr int kMaxBlock = 1024;
 static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool tile_ok, int64_t nshots, int cus,
                         int spb) {
-  constexpr int kMinThreads = 40, kFewWaves = 4;
+  constexpr int kFewWaves = 4;
   auto threads = [&](int cpt) { return (c.m + cpt - 1) / cpt; };
   auto usable = [&](int cpt) {
     return threads(cpt) * std::max(spb, 1) <= kMaxBlock && find_variant(dc, dv, cpt, bp, reg);
@@ -1589,11 +1599,15 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
   } else if (tile_ok) {
     full = 8;
   } else {
-    const bool wide_pad = !reg && dv == 4;
-    const int most = wide_pad ? (c.m > 256 ? 2 : 1) : !reg || dc == 2 ? 4 : dv >= 3 ? 1 : dc == 6 ? 4 : 8;
-    const int least = dc == 2 ? 24 : kMinThreads;
+    auto pays = [&](int a) {
+      if (dc == 2) return a <= 4 && threads(a) >= 24;
+      if (dc == 4 && dv == 2) return threads(a) >= 40;
+      if (dv == 2) return a <= 4 && threads(a) >= (a == 4 ? 100 : 40);
+      if (dc == 4) return a == 2 && c.m > 256 && c.m <= 512 && 2 * ((threads(2) + 63) / 64) <= (c.m + 63) / 64;
+      return a == 2 && c.m > 256;
+    };
     for (int a : order)
-      if (usable(a) && (!full || (a <= most && threads(a) >= least))) full = a;
+      if (usable(a) && (!full || pays(a))) full = a;
   }
   for (int i = 3; i >= 0 && !full; --i)  // none of those: the most checks per thread (the caller checks the block)
     if (find_variant(dc, dv, order[i], bp, reg)) full = order[i];

@@ -72,3 +72,12 @@ def shape_of(shapes, m, dc, dv, regular, bp, nshots, per=2):
 def test_padded_degree_8_min_sum_never_takes_four_checks_per_thread(shapes, nshots):
     for m in (100, 200, 256, 257, 448, 600, 900, 1024):
         assert shape_of(shapes, m, 8, 4, 0, 0, nshots)[1] == (1 if m <= 256 else 2), m
+
+
+@pytest.mark.parametrize("dc,dv,m,cpt", [
+    (6, 3, 252, 1), (6, 3, 257, 2), (6, 3, 378, 2), (6, 3, 900, 2), (4, 4, 192, 1), (4, 4, 375, 2), (4, 4, 512, 2),
+    (4, 4, 513, 1), (4, 4, 648, 1), (6, 2, 216, 2), (6, 2, 343, 2), (6, 2, 396, 2), (6, 2, 397, 4), (6, 2, 512, 4),
+    (4, 2, 441, 8), (4, 2, 169, 4), (2, 2, 101, 4), (2, 2, 31, 1)])
+def test_checks_per_thread_of_a_full_device_min_sum(shapes, dc, dv, m, cpt):
+    assert shape_of(shapes, m, dc, dv, 1, 0, 0, per=1)[1] == cpt
+    assert shape_of(shapes, m, dc, dv, 1, 0, 65536, per=1)[1] == cpt
