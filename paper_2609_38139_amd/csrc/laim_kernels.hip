@@ -1542,6 +1542,12 @@ int device_cus(int device) {
   return cus;
 }
 
+// Whether the wavefronts of nshots shots of th threads number at most per_simd
+// (shots of a part wavefront share one); no shots stand for a full device.
+static bool few_waves(int64_t nshots, int th, int per_simd, int cus) {
+  return nshots > 0 && nshots * (th < 64 ? th : (th + 63) / 64 * 64) <= (int64_t)per_simd * 4 * 64 * cus;
+}
+
 // Checks per thread by the built-in rule, for nshots shots (0: a batch that
 // fills the device). Fewer checks per thread make a sweep of one shot shorter
 // (a wavefront alone issues one instruction in about 5 clocks, so a thread's
@@ -1574,7 +1580,7 @@ int device_cus(int device) {
 //    toric L = 32, 16,384 shots 23.8 / 21.9 / 23.4 / 30.5; 3D point L = 12, 4,096
 //    shots - / 36.9 / 34.0 / 39.4); checks of degree 2 have no box-plus step
 //    and follow the min-sum rule.
-//  - Otherwise the fewest whose wavefronts number at most kFewWaves per SIMD
+//  - Otherwise the fewest whose wavefronts number at most 4 per SIMD: few_waves
 //    (2D toric L = 16, min-sum, 1,024 shots, 4 per SIMD at one check per thread:
 //    0.090 ms against 0.205 with the tiled variant; 4,096 shots, 4 per SIMD at
 //    four, 0.161 against 0.230; L = 8, 16,384 shots 0.167 with four checks per
@@ -1586,7 +1592,6 @@ int device_cus(int device) {
 constexpr int kMaxBlock = 1024;
 static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool tile_ok, int64_t nshots, int cus,
                         int spb) {
-  constexpr int kFewWaves = 4;
   auto threads = [&](int cpt) { return (c.m + cpt - 1) / cpt; };
   auto usable = [&](int cpt) {
     return threads(cpt) * std::max(spb, 1) <= kMaxBlock && find_variant(dc, dv, cpt, bp, reg);
@@ -1611,12 +1616,8 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
   }
   for (int i = 3; i >= 0 && !full; --i)  // none of those: the most checks per thread (the caller checks the block)
     if (find_variant(dc, dv, order[i], bp, reg)) full = order[i];
-  if (nshots > 0)
-    for (int a : order) {
-      const int th = threads(a);
-      const int64_t lanes = nshots * (th < 64 ? th : (th + 63) / 64 * 64);  // shots of a part wavefront share one
-      if (a < full && usable(a) && lanes <= (int64_t)kFewWaves * 4 * 64 * cus) return a;
-    }
+  for (int a : order)
+    if (a < full && usable(a) && few_waves(nshots, threads(a), 4, cus)) return a;
   return full;
 }
 
@@ -1638,13 +1639,8 @@ static bool pairs_pay(const DevCode& c, int bp, int dc, int dv, int reg, int64_t
 // Shots per block by the built-in rule: fills the wavefronts of a block of
 // at most 256 threads, the fewest shots first (each further one has to add 2%
 // of lanes in use: the shots of a block run in lockstep and wait for the
-// slowest). [[144,12,12]] (72 threads) takes 3, [[72,12,6]] (36) 7, 125 threads
-// one (3D point L = 5, min-sum, 16,384 shots: 0.56 ms as 63 x 2 x 1 against 0.81
-// as 125 x 1 x 2). At least `least`: a claim of the shot queue takes 13 ns whatever
-// it claims, which bounds min-sum on small codes, so with more than 16 blocks per CU a block has
-// 96 checks or more (65,536 shots, ms with one shot per block and with two: 2D
-// toric L = 8, 64 checks, 0.85 / 0.57; 3D point L = 4, 64 checks, 0.92 / 0.73;
-// L = 5, 125 checks, 1.37 / 1.59).
+// slowest). [[144,12,12]] (72 threads) takes 3, [[72,12,6]] (36) 7, 125 checks on
+// 63 threads one. At least `least`.
 static int built_in_spb(int nt, int least) {
   int best = 1;
   double most = -1.0;
@@ -1678,9 +1674,9 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
   // min-sum on the 2D toric layout: the tiled variant, on a full device faster
   // than the other shapes at every L measured (8 to 64)
   const bool tile_ok = c.tile_chk && bp == 0 && dc == 4 && dv == 2 && reg && !seq;
+  const int cus = device_cus(device);
   int lpc = 1;
   if (cpt <= 0 && nt <= 0) {
-    const int cus = device_cus(device);
     cpt = built_in_cpt(c, bp, dc, dv, reg, tile_ok, nshots, cus, spb);
     if (pairs_pay(c, bp, dc, dv, reg, nshots, cus, spb)) {
       cpt = 1;
@@ -1738,11 +1734,22 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
     spb = best > 0 ? best : 1;
   }
   if (spb <= 0) {
+    // A claim of the shot queue takes 13 ns whatever it claims, which bounds
+    // min-sum on small codes: a block has shots of at least 576 messages in all,
+    // as far as the batch has 8 blocks per CU of them. Not with at most 6 wavefronts
+    // per SIMD, where every block runs at once and there is no queue (d = 31, 12,000
+    // shots: 2 and 6 a block 47 / 52 and 33 / 37 us). (32,768 shots, 32 rounds at
+    // the codes' usual noise and 8 rounds at a fifth of it, us with 96 checks in a
+    // block instead and so: repetition d = 31, 31 threads, 4 and 8 shots 169 / 131 and
+    // 144 / 87; d = 64, 32 threads, 2 and 6 275 / 143 and 275 / 110; 2D toric L = 5, 25
+    // threads, 5 and 10 141 / 142 and 133 / 104; L = 11, 61 threads, 1 and 2 486 / 399
+    // and 458 / 255. More do not pay: 3D point L = 5, 63 threads, 750 messages, 1 and 2
+    // 659 / 745 and 465 / 282.)
     int64_t least = 1;
-    if ((bp == 0 || dc == 2) && lpc == 1) {
-      least = (96 + nt * cpt - 1) / (nt * cpt);
-      const int64_t room = nshots / (16 * (int64_t)device_cus(device));  // 0 shots: a full device
-      if (nshots > 0 && least > room) least = room > 1 ? room : 1;
+    if ((bp == 0 || dc == 2) && lpc == 1 && !few_waves(nshots, nt, 6, cus)) {
+      least = (576 + c.m * dc - 1) / (c.m * dc);
+      const int64_t room = nshots / (8 * (int64_t)cus);  // 0 shots: a full device
+      if (nshots > 0 && least > room) least = std::max<int64_t>(room, 1);
     }
     spb = built_in_spb(nt, (int)least);
     // as many as the LDS holds (and not more than there are)

@@ -81,3 +81,12 @@ def test_padded_degree_8_min_sum_never_takes_four_checks_per_thread(shapes, nsho
 def test_checks_per_thread_of_a_full_device_min_sum(shapes, dc, dv, m, cpt):
     assert shape_of(shapes, m, dc, dv, 1, 0, 0, per=1)[1] == cpt
     assert shape_of(shapes, m, dc, dv, 1, 0, 65536, per=1)[1] == cpt
+
+
+@pytest.mark.parametrize("dc,dv,m,nshots,spb", [
+    (2, 2, 9, 65536, 28), (2, 2, 15, 32768, 17), (2, 2, 31, 8192, 2), (2, 2, 31, 12000, 2), (2, 2, 31, 16384, 8), (2, 2, 31, 65536, 8),
+    (2, 2, 64, 16384, 6), (2, 2, 64, 65536, 6), (2, 2, 101, 65536, 7), (4, 2, 25, 8192, 5), (4, 2, 25, 16384, 10),
+    (4, 2, 25, 65536, 10), (4, 2, 121, 8192, 2), (4, 2, 121, 65536, 2), (6, 2, 64, 65536, 2), (6, 2, 125, 65536, 1),
+    (6, 3, 72, 65536, 3), (6, 3, 36, 65536, 7), (4, 4, 81, 65536, 3), (4, 4, 192, 65536, 1), (2, 2, 9, 0, 28)])
+def test_shots_per_block_of_small_codes(shapes, dc, dv, m, nshots, spb):
+    assert shape_of(shapes, m, dc, dv, 1, 0, nshots, per=1)[3] == spb
