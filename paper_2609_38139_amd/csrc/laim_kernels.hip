@@ -1627,13 +1627,16 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
 // blocks of at most 900 threads, past which one block alone keeps every SIMD
 // busy (ms at one and two lanes: 2D toric L = 16, 16 / 1,024 / 4,096 shots
 // 0.28 / 0.58 / 1.69 and 0.23 / 0.54 / 1.81; 3D point L = 8, 512 checks, 256 shots
-// 0.99 and 1.11) -- and on (6, 3) codes always: a few shots that never clear
-// set the end of a launch of their short shots ([[144,12,12]], 65,536 shots, p =
-// 0.03: 5.29 and 3.70; [[72,12,6]] 0.85 and 0.78).
+// 0.99 and 1.11) -- and at any batch size on (6, 3) codes of at most 320 threads: a
+// few shots that never clear set the end of a launch of their short shots (ms
+// at one and two lanes, 32,768 shots, p = 0.03, 32 rounds and p = 0.006, 8 rounds: 36
+// checks 0.57 / 0.52 and 0.25 / 0.22, 72 2.09 / 1.60 and 0.47 / 0.44, 144 3.35 / 3.11
+// and 1.13 / 1.15; 180 checks 3.68 / 4.42 and 1.15 / 1.67, 288 7.96 / 9.94 and 2.98 /
+// 4.08, 432 9.64 / 13.8 and 3.92 / 5.92).
 static bool pairs_pay(const DevCode& c, int bp, int dc, int dv, int reg, int64_t nshots, int cus, int spb) {
   if (bp != 1 || 2 * c.m > 900 || 2 * c.m * std::max(spb, 1) > kMaxBlock || !find_variant(dc, dv, 1, bp, reg, 0, 2))
     return false;
-  return dv == 3 || (nshots > 0 && nshots * ((c.m + 63) / 64) <= (int64_t)8 * 4 * cus);
+  return (dv == 3 && 2 * c.m <= 320) || (nshots > 0 && nshots * ((c.m + 63) / 64) <= (int64_t)8 * 4 * cus);
 }
 
 // Shots per block by the built-in rule: fills the wavefronts of a block of

@@ -90,3 +90,10 @@ def test_checks_per_thread_of_a_full_device_min_sum(shapes, dc, dv, m, cpt):
     (6, 3, 72, 65536, 3), (6, 3, 36, 65536, 7), (4, 4, 81, 65536, 3), (4, 4, 192, 65536, 1), (2, 2, 9, 0, 28)])
 def test_shots_per_block_of_small_codes(shapes, dc, dv, m, nshots, spb):
     assert shape_of(shapes, m, dc, dv, 1, 0, nshots, per=1)[3] == spb
+
+
+@pytest.mark.parametrize("m,nshots,lanes", [(36, 65536, 2), (72, 65536, 2), (160, 65536, 2), (161, 65536, 1),
+                                            (180, 32768, 1), (432, 32768, 1), (432, 0, 1), (432, 1024, 2),
+                                            (432, 2048, 1), (450, 256, 2), (451, 256, 1), (72, 0, 2)])
+def test_two_lanes_per_check_on_6_3_codes(shapes, m, nshots, lanes):
+    assert shape_of(shapes, m, 6, 3, 1, 1, nshots)[2] == lanes
