@@ -1561,17 +1561,19 @@ static bool few_waves(int64_t nshots, int th, int per_simd, int cus) {
 //    / 0.91 / 0.82 / 0.82); the tiled variant always 8.
 //    (2, 2): up to 4 with at least 24 threads (repetition d = 101, 131,072 shots
 //    1.56 / 0.70 / 0.71 / 0.86).
-//    (6, 2), padded or not: 2 with 40 threads, 4 with 100 (3D point, 32,768 shots,
-//    p = 0.02: L = 6, 216 checks, - / 1.37 / 1.33, of 8,192 shots 0.56 / 0.67; L = 7,
-//    343 checks, - / 2.78 / 3.03; L = 8, 512 checks, 6.69 / 4.46 / 3.76; L = 12, 8,192
-//    shots - / 25.1 / 18.0 / 19.3, 36 spills).
+//    (6, 2), padded or not: 2 with 40 threads, 4 with 100, or with 40 where 4 halve
+//    the wavefronts and leave 48 per SIMD (3D point, p = 0.02: L = 6, 216 checks,
+//    65,536 shots - / 2.46 / 2.27, 32,768 - / 1.37 / 1.33, 8,192 - / 0.56 / 0.67;
+//    L = 7, 343 checks, 32,768 shots - / 2.78 / 3.03; L = 8, 512 checks, 6.69 / 4.46 /
+//    3.76; L = 12, 8,192 shots - / 25.1 / 18.0 / 19.3, 36 spills).
 //    (6, 3): 1 up to 256 checks, 2 above (8,192 shots at p = 0.006, 8 rounds: 252
 //    checks 0.18 / 0.18, 324 0.37 / 0.25, 378 0.38 / 0.24, 900 1.29 / 0.90; at p =
 //    0.03, 32 rounds: 252 0.49 / 0.57, 324 0.71 / 0.68, 378 0.81 / 0.73, 900 2.33 / 1.75;
 //    [[144,12,12]], 131,072 shots 1.71 / 1.94 / 3.75).
-//    (4, 4): 1, but 2 for 257 to 512 checks if that takes half the wavefronts
-//    (membrane, 32,768 shots, p = 0.03 and 0.006: L = 5, 375 checks, 0.94 / 0.74 and
-//    0.58 / 0.43; L = 4, 192 checks, 0.64 / 0.72 and 0.41 / 0.42; L = 6, 648 checks in
+//    (4, 4): 1, but 2 for 257 to 512 checks if that takes half the wavefronts and
+//    1 would make 32 or more per SIMD (membrane, p = 0.03 and 0.006: L = 5, 375
+//    checks, 32,768 shots 0.94 / 0.74 and 0.58 / 0.43, 8,192 0.43 / 0.48 and 0.17 / 0.14,
+//    2,048 0.13 / 0.14 and 0.067 / 0.072; 32,768 shots L = 4, 192 checks, 0.64 / 0.72 and 0.41 / 0.42; L = 6, 648 checks in
 //    11 or 6 wavefronts, 2.02 / 2.21 / 2.37 and 1.15 / 1.22 / 1.05).
 //    Padded (8, 4): 1 up to 256 checks, 2 above; 4 spills most of its 96 partner
 //    addresses (mixed degrees 3 to 8, 8,192 shots: 200 checks 0.72 / 1.02 / 4.79,
@@ -1604,11 +1606,16 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
   } else if (tile_ok) {
     full = 8;
   } else {
+    auto waves = [&](int a) { return (threads(a) + 63) / 64; };
+    auto halves = [&](int a) { return 2 * waves(a) <= waves(a / 2); };
     auto pays = [&](int a) {
       if (dc == 2) return a <= 4 && threads(a) >= 24;
       if (dc == 4 && dv == 2) return threads(a) >= 40;
-      if (dv == 2) return a <= 4 && threads(a) >= (a == 4 ? 100 : 40);
-      if (dc == 4) return a == 2 && c.m > 256 && c.m <= 512 && 2 * ((threads(2) + 63) / 64) <= (c.m + 63) / 64;
+      if (dv == 2)
+        return a <= 4 && (threads(a) >= (a == 4 ? 100 : 40) ||
+                          (threads(a) >= 40 && halves(a) && !few_waves(nshots, 64 * waves(a), 48, cus)));
+      if (dc == 4)
+        return a == 2 && c.m > 256 && c.m <= 512 && halves(a) && !few_waves(nshots, 64 * waves(1), 31, cus);
       return a == 2 && c.m > 256;
     };
     for (int a : order)

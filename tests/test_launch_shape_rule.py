@@ -76,7 +76,7 @@ def test_padded_degree_8_min_sum_never_takes_four_checks_per_thread(shapes, nsho
 
 @pytest.mark.parametrize("dc,dv,m,cpt", [
     (6, 3, 252, 1), (6, 3, 257, 2), (6, 3, 378, 2), (6, 3, 900, 2), (4, 4, 192, 1), (4, 4, 375, 2), (4, 4, 512, 2),
-    (4, 4, 513, 1), (4, 4, 648, 1), (6, 2, 216, 2), (6, 2, 343, 2), (6, 2, 396, 2), (6, 2, 397, 4), (6, 2, 512, 4),
+    (4, 4, 513, 1), (4, 4, 648, 1), (6, 2, 216, 4), (6, 2, 343, 2), (6, 2, 397, 4), (6, 2, 512, 4),
     (4, 2, 441, 8), (4, 2, 169, 4), (2, 2, 101, 4), (2, 2, 31, 1)])
 def test_checks_per_thread_of_a_full_device_min_sum(shapes, dc, dv, m, cpt):
     assert shape_of(shapes, m, dc, dv, 1, 0, 0, per=1)[1] == cpt
@@ -97,3 +97,10 @@ def test_shots_per_block_of_small_codes(shapes, dc, dv, m, nshots, spb):
                                             (432, 2048, 1), (450, 256, 2), (451, 256, 1), (72, 0, 2)])
 def test_two_lanes_per_check_on_6_3_codes(shapes, m, nshots, lanes):
     assert shape_of(shapes, m, 6, 3, 1, 1, nshots)[2] == lanes
+
+
+@pytest.mark.parametrize("dc,dv,m,nshots,cpt", [
+    (6, 2, 216, 8192, 2), (6, 2, 216, 49152, 2), (6, 2, 216, 49153, 4), (6, 2, 343, 1 << 20, 2),
+    (4, 4, 375, 5290, 1), (4, 4, 375, 5500, 2), (4, 4, 375, 1024, 1)])
+def test_checks_per_thread_by_the_wavefronts_in_flight(shapes, dc, dv, m, nshots, cpt):
+    assert shape_of(shapes, m, dc, dv, 1, 0, nshots, per=1)[1] == cpt
