@@ -203,9 +203,9 @@ typedef struct {
 /* Execution forms of laim_decode_rounds; all give identical results. */
 #define LAIM_FORM_AUTO 0     /* resident if the code fits in LDS (and, for min-sum,
                                 alpha <= 1), else stream; larger regular codes of the
-                                compiled degrees run one block per shot with their
-                                messages in LDS and device memory (the workspace and
-                                sweeps_out are the stream form's) */
+                                compiled degrees run, where that is faster, one block
+                                per shot with their messages in LDS and device memory
+                                (the workspace and sweeps_out are the stream form's) */
 #define LAIM_FORM_RESIDENT 1 /* one persistent launch, per-shot state in LDS/registers */
 #define LAIM_FORM_STREAM 2   /* messages in HBM, one launch per BP sweep and per phase */
 

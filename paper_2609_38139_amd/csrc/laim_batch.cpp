@@ -204,7 +204,7 @@ laim_status laim_batch_plan_create(const laim_batch_item* items, int32_t nitems,
     const laim_batch_item& b = items[stream_items[k].index];
     if (b.nshots == 0) continue;
     const KParams& kp = stream_items[k].kp;
-    e = wide_ok(b.code->dev, kp)
+    e = wide_ok(b.code->dev, kp, b.nshots)
             ? launch_wide(b.code->dev, kp, b.e0, b.shot0, b.nshots, base + stream_off[k],
                           stream_workspace_bytes(b.code->dev, b.nshots, false), b.z_out, b.s_out, b.tclr_out, nullptr,
                           plan->cap)

@@ -734,7 +734,7 @@ laim_status decode_common(const laim_code* code, const laim_decode_params* param
     er = launch_resident(code->dev, kp, sh, e0, shot0, nshots, ws, z_out, s_out, tclr_out, L_out,
                          fused_fail ? fail_out : nullptr, sweeps_out, (hipStream_t)stream);
   } else {
-    er = (form == LAIM_FORM_AUTO && wide_ok(code->dev, kp))
+    er = (form == LAIM_FORM_AUTO && wide_ok(code->dev, kp, nshots))
              ? launch_wide(code->dev, kp, e0, shot0, nshots, ws, need, z_out, s_out, tclr_out, L_out, (hipStream_t)stream)
              : launch_stream(code->dev, kp, e0, shot0, nshots, ws, z_out, s_out, tclr_out, L_out, (hipStream_t)stream);
     if (er == hipSuccess) er = launch_sweep_count(kp, tclr_out, nshots, sweeps_out, (hipStream_t)stream);

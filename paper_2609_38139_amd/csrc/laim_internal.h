@@ -148,7 +148,7 @@ hipError_t launch_stream(const DevCode& c, const KParams& kp, const uint8_t* e0,
 // ---- the wide form (laim_wide.hip): regular codes of more than
 // kWideMinChecks checks that cannot run resident, under AUTO only
 constexpr int32_t kWideMinChecks = 4096;
-bool wide_ok(const DevCode& c, const KParams& kp);
+bool wide_ok(const DevCode& c, const KParams& kp, int32_t nshots);
 // ws: at least stream_workspace_bytes for the same shots
 hipError_t launch_wide(const DevCode& c, const KParams& kp, const uint8_t* e0, uint64_t shot0, int32_t nshots,
                        void* ws, size_t ws_bytes, uint8_t* z, uint8_t* s, int32_t* tclr, float* L, hipStream_t st,

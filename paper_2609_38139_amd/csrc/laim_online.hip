@@ -370,7 +370,7 @@ laim_status laim_decode_online(const laim_online_plan* plan, const laim_decode_p
     if (res)
       er = launch_resident(wc->dev, kp, sh, nullptr, shot0, nshots, w.dec, w.zw, w.sout, w.tclr, nullptr,
                            nullptr, nullptr, s, w.sw, k * kp.rounds);
-    else if (wide_ok(wc->dev, kp))
+    else if (wide_ok(wc->dev, kp, nshots))
       er = launch_wide(wc->dev, kp, nullptr, shot0, nshots, w.dec,
                        stream_workspace_bytes(wc->dev, nshots, false), w.zw, w.sout, w.tclr, nullptr, s, w.sw,
                        k * kp.rounds);

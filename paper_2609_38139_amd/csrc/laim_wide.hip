@@ -519,9 +519,24 @@ size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 // irregular codes keep the stream form; so do codes of at most 4,096 checks,
 // which run resident but for those cases and would leave threads of a block
 // without a check.
-bool wide_ok(const DevCode& c, const KParams& kp) {
+// Codes of qubit degree 2 or 3 with more than half of their messages past the
+// LDS (which holds about 38,000) run faster in the stream form once there are
+// more shots than half of one of its tiles. Measured, ms in the stream form and
+// here, 1,024 shots, min-sum, 4 rounds: 2D toric L = 150, 90,000 messages, 11.9 /
+// 11.8; L = 160, 102,400, 13.4 / 14.9; L = 180, 129,600, 17.1 / 21.8; 3D point L = 24,
+// 82,944, 11.1 / 9.3; L = 26, 105,456, 14.0 / 15.6; bicycle codes, 98,304 15.7 / 13.2 and
+// 153,600 24.4 / 27.7. Sum-product, L = 150 16.5 / 16.3, L = 176 22.8 / 23.9. Up to 128
+// shots this form was the faster one at every size, and membrane codes (qubit degree 4)
+// at every number of shots up to L = 22, 127,776 messages, 21.7 / 17.6.
+static bool wide_pays(const DevCode& c, int32_t nshots) {
+  const int64_t most = c.dvmax == 2 ? 92000 : c.dvmax == 3 ? 110000 : INT64_MAX;
+  return nshots <= 128 || (int64_t)c.m * c.dcmax <= most;
+}
+
+bool wide_ok(const DevCode& c, const KParams& kp, int32_t nshots) {
   return c.regular && c.m > kWideMinChecks && c.m <= kWideMaxChecks && c.n <= kWideMaxQubits &&
-         kp.conflict != kConflictSequential && !(kp.bp == 0 && kp.alpha > 1.0f) && wide_variant(c, kp.bp) != nullptr;
+         kp.conflict != kConflictSequential && !(kp.bp == 0 && kp.alpha > 1.0f) && wide_pays(c, nshots) &&
+         wide_variant(c, kp.bp) != nullptr;
 }
 
 hipError_t launch_wide(const DevCode& c, const KParams& kp, const uint8_t* e0, uint64_t shot0, int32_t nshots,

@@ -11,11 +11,10 @@ PKG = os.path.join(ROOT, "paper_2609_38139_amd")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
-@pytest.fixture(scope="module")
-def shapes(tmp_path_factory):
-    exe = str(tmp_path_factory.mktemp("shapes") / "shapes")
+def build(tmp, name):
+    exe = str(tmp / name)
     subprocess.run([HIPCC, "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
-                    os.path.join(HERE, "launch_shape", "shapes.cpp"), "-o", exe, "-L", PKG, "-llaim",
+                    os.path.join(HERE, "launch_shape", name + ".cpp"), "-o", exe, "-L", PKG, "-llaim",
                     f"-Wl,-rpath,{PKG}"], check=True)
 
     def run(lines):
@@ -23,6 +22,16 @@ def shapes(tmp_path_factory):
                            text=True, check=True)
         return [[int(v) for v in row.split()] for row in r.stdout.strip().split("\n")]
     return run
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    return build(tmp_path_factory.mktemp("shapes"), "shapes")
+
+
+@pytest.fixture(scope="module")
+def wide(tmp_path_factory):
+    return build(tmp_path_factory.mktemp("wide"), "wide")
 
 
 # (check degree, qubit degree, regular, on the 2D toric lattice, qubits per check)
@@ -104,3 +113,13 @@ def test_two_lanes_per_check_on_6_3_codes(shapes, m, nshots, lanes):
     (4, 4, 375, 5290, 1), (4, 4, 375, 5500, 2), (4, 4, 375, 1024, 1)])
 def test_checks_per_thread_by_the_wavefronts_in_flight(shapes, dc, dv, m, nshots, cpt):
     assert shape_of(shapes, m, dc, dv, 1, 0, nshots, per=1)[1] == cpt
+
+
+def test_wide_form_by_messages_and_shots(wide):
+    rows = [((4900, 9800, 4, 2), 1, 1), ((22500, 45000, 4, 2), 1, 1), ((25600, 51200, 4, 2), 1, 0),
+            ((32400, 64800, 4, 2), 1, 0), ((13824, 41472, 6, 2), 1, 1), ((17576, 52728, 6, 2), 1, 0),
+            ((16384, 32768, 6, 3), 1, 1), ((25600, 51200, 6, 3), 1, 0), ((31944, 31944, 4, 4), 1, 1),
+            ((4096, 8192, 4, 2), 0, 0), ((33000, 33000, 4, 4), 0, 0)]
+    cases = [(code + (bp, n), few if n <= 128 else many)
+             for code, few, many in rows for bp in (0, 1) for n in (1, 128, 129, 1024, 65536)]
+    assert [r[0] for r in wide([c for c, _ in cases])] == [want for _, want in cases]
