@@ -309,6 +309,24 @@ laim_status laim_resident_variant(const laim_code* code, const laim_decode_param
                                   const laim_resident_cfg* cfg, int32_t* dc, int32_t* dv,
                                   int32_t* checks_per_thread, int32_t* tiled);
 
+/* laim_launch_shape -- what laim_decode_rounds in `form` (or, with cfg,
+ * laim_decode_rounds_cfg) runs for these parameters and nshots shots. A plan
+ * group, an online window and a server choose by the same rules. Errors: those
+ * of the decode call for the same arguments. */
+#define LAIM_FORM_WIDE 3 /* reported only: AUTO's one block per shot for larger codes */
+typedef struct {
+  int32_t form; /* LAIM_FORM_RESIDENT, LAIM_FORM_STREAM or LAIM_FORM_WIDE */
+  /* the resident form's shape (0 in the other forms) */
+  int32_t threads_per_shot;
+  int32_t checks_per_thread;
+  int32_t shots_per_block;
+  int32_t lanes_per_check; /* 1, or 2 threads sharing every check */
+  int32_t tiled;           /* 1: the tiled variant */
+} laim_launch_info;
+laim_status laim_launch_shape(const laim_code* code, const laim_decode_params* params,
+                              const laim_resident_cfg* cfg, int32_t nshots, int32_t form,
+                              laim_launch_info* out);
+
 /* Sets the resident launch shape used from now on for this code and BP
  * rule (the autotuner's choice); cfg = NULL restores the built-in rule. On a
  * batch that fills the device: min-sum on the 2D toric layout takes the tiled

@@ -667,6 +667,39 @@ size_t laim_workspace_bytes(const laim_code* code, const laim_decode_params* par
 
 namespace laim {
 
+// The form a decode of nshots shots runs (LAIM_FORM_WIDE among them) and, for the
+// resident one, its shape.
+static laim_status choose_form(const laim_code* code, const KParams& kp, int32_t nshots, int32_t form,
+                               const laim_resident_cfg* cfg, ResidentShape* sh, int* f) {
+  const bool seq = kp.conflict == kConflictSequential;
+  // The resident min-sum kernel relies on alpha <= 1 (its outputs cannot
+  // reach the clamp); other scales run in the stream form.
+  const bool resident_ok = !(kp.bp == 0 && kp.alpha > 1.0f);
+  if (cfg) {
+    if (!resident_ok) {
+      set_error("the resident min-sum form needs alpha <= 1");
+      return LAIM_EUNSUP;
+    }
+    if (!resident_shape(code->dev, kp.bp, cfg, sh, code->device, seq, reg_dv2_ok(kp), nshots)) return LAIM_EINVAL;
+    *f = LAIM_FORM_RESIDENT;
+  } else if (!resident_ok) {
+    if (form == LAIM_FORM_RESIDENT) {
+      set_error("the resident min-sum form needs alpha <= 1");
+      return LAIM_EUNSUP;
+    }
+    *f = LAIM_FORM_STREAM;
+  } else {
+    *f = resolve_form(code, kp.bp, seq, reg_dv2_ok(kp), form, nshots, sh);
+    if (*f < 0) {
+      set_error("the code cannot run in the resident form (a shot's state exceeds the LDS or its "
+                "degrees have no compiled variant)");
+      return LAIM_EUNSUP;
+    }
+  }
+  if (*f == LAIM_FORM_STREAM && form == LAIM_FORM_AUTO && wide_ok(code->dev, kp, nshots)) *f = LAIM_FORM_WIDE;
+  return LAIM_OK;
+}
+
 laim_status decode_common(const laim_code* code, const laim_decode_params* params,
                                  const uint8_t* e0, uint64_t shot0, int32_t nshots, void* ws,
                                  size_t ws_bytes, uint8_t* z_out, uint8_t* s_out, int32_t* tclr_out,
@@ -688,35 +721,13 @@ laim_status decode_common(const laim_code* code, const laim_decode_params* param
     return LAIM_EUNSUP;
   }
   if (nshots == 0) return LAIM_OK;
-  const bool seq = kp.conflict == kConflictSequential;
   ResidentShape sh;
   int f;
-  // The resident min-sum kernel relies on alpha <= 1 (its outputs cannot
-  // reach the clamp); other scales run in the stream form.
-  const bool resident_ok = !(kp.bp == 0 && kp.alpha > 1.0f);
-  if (cfg) {
-    if (!resident_ok) {
-      set_error("the resident min-sum form needs alpha <= 1");
-      return LAIM_EUNSUP;
-    }
-    if (!resident_shape(code->dev, kp.bp, cfg, &sh, code->device, seq, reg_dv2_ok(kp), nshots)) return LAIM_EINVAL;
-    f = LAIM_FORM_RESIDENT;
-  } else if (!resident_ok) {
-    if (form == LAIM_FORM_RESIDENT) {
-      set_error("the resident min-sum form needs alpha <= 1");
-      return LAIM_EUNSUP;
-    }
-    f = LAIM_FORM_STREAM;
-  } else {
-    f = resolve_form(code, kp.bp, seq, reg_dv2_ok(kp), form, nshots, &sh);
-    if (f < 0) {
-      set_error("the code cannot run in the resident form (a shot's state exceeds the LDS or its "
-                "degrees have no compiled variant)");
-      return LAIM_EUNSUP;
-    }
-  }
+  st = choose_form(code, kp, nshots, form, cfg, &sh, &f);
+  if (st != LAIM_OK) return st;
   const size_t need = (f == LAIM_FORM_RESIDENT) ? resident_workspace_bytes()
-                                                : stream_workspace_bytes(code->dev, nshots, seq);
+                                                : stream_workspace_bytes(code->dev, nshots,
+                                                                         kp.conflict == kConflictSequential);
   if (!ws || ws_bytes < need) {
     set_error("workspace of %zu bytes needed (got %zu)", need, ws_bytes);
     return LAIM_ENOMEM;
@@ -734,7 +745,7 @@ laim_status decode_common(const laim_code* code, const laim_decode_params* param
     er = launch_resident(code->dev, kp, sh, e0, shot0, nshots, ws, z_out, s_out, tclr_out, L_out,
                          fused_fail ? fail_out : nullptr, sweeps_out, (hipStream_t)stream);
   } else {
-    er = (form == LAIM_FORM_AUTO && wide_ok(code->dev, kp, nshots))
+    er = f == LAIM_FORM_WIDE
              ? launch_wide(code->dev, kp, e0, shot0, nshots, ws, need, z_out, s_out, tclr_out, L_out, (hipStream_t)stream)
              : launch_stream(code->dev, kp, e0, shot0, nshots, ws, z_out, s_out, tclr_out, L_out, (hipStream_t)stream);
     if (er == hipSuccess) er = launch_sweep_count(kp, tclr_out, nshots, sweeps_out, (hipStream_t)stream);
@@ -747,6 +758,25 @@ laim_status decode_common(const laim_code* code, const laim_decode_params* param
 }  // namespace laim
 
 extern "C" {
+
+laim_status laim_launch_shape(const laim_code* code, const laim_decode_params* params,
+                              const laim_resident_cfg* cfg, int32_t nshots, int32_t form,
+                              laim_launch_info* out) {
+  if (!code || !params || !out || nshots < 0 || form < LAIM_FORM_AUTO || form > LAIM_FORM_STREAM) {
+    set_error("laim_launch_shape: bad arguments");
+    return LAIM_EINVAL;
+  }
+  KParams kp;
+  laim_status st = resolve_params(params, &kp);
+  if (st != LAIM_OK) return st;
+  ResidentShape sh;
+  int f;
+  st = choose_form(code, kp, nshots, form, cfg, &sh, &f);
+  if (st != LAIM_OK) return st;
+  *out = laim_launch_info{f, 0, 0, 0, 0, 0};
+  if (f == LAIM_FORM_RESIDENT) *out = laim_launch_info{f, sh.nt, sh.cpt, sh.spb, sh.lpc, sh.tile};
+  return LAIM_OK;
+}
 
 laim_status laim_decode_rounds(const laim_code* code, const laim_decode_params* params,
                                const uint8_t* e0, uint64_t shot0, int32_t nshots, void* workspace,

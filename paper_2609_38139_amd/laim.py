@@ -19,6 +19,7 @@ LIB_PATH = os.path.join(HERE, "liblaim.so")
 
 OK, EINVAL, ENOMEM, EHIP, EUNSUP, EBUSY = 0, -1, -2, -3, -4, -5
 FORM_AUTO, FORM_RESIDENT, FORM_STREAM = 0, 1, 2
+FORM_WIDE = 3  # reported by Code.launch_shape only
 FORMS = {"auto": FORM_AUTO, "resident": FORM_RESIDENT, "stream": FORM_STREAM}
 
 # Every symbol the header declares (checked by the tests).
@@ -32,7 +33,7 @@ SYMBOLS = [
     "laim_server_result", "laim_server_stats", "laim_server_destroy", "laim_decode_continuous",
     "laim_decode_bitcentric", "laim_decode_rounds_static", "laim_online_plan_create",
     "laim_online_plan_destroy", "laim_online_workspace_bytes", "laim_decode_online",
-    "laim_decode_bitcentric_form", "laim_resident_variant",
+    "laim_decode_bitcentric_form", "laim_resident_variant", "laim_launch_shape",
 ]
 
 STATIC_SCRATCH_BYTES = 32 << 20  # LAIM_STATIC_SCRATCH_BYTES
@@ -61,6 +62,11 @@ MOVES = {"single": 0, "multi": 1}
 class ResidentCfg(C.Structure):
     _fields_ = [("threads_per_shot", C.c_int32), ("checks_per_thread", C.c_int32),
                 ("shots_per_block", C.c_int32)]
+
+
+class LaunchInfo(C.Structure):
+    _fields_ = [("form", C.c_int32), ("threads_per_shot", C.c_int32), ("checks_per_thread", C.c_int32),
+                ("shots_per_block", C.c_int32), ("lanes_per_check", C.c_int32), ("tiled", C.c_int32)]
 
 
 class BatchItem(C.Structure):
@@ -210,6 +216,8 @@ def lib():
         L.laim_decode_bitcentric.argtypes = [vp, C.c_double, vp, i32, i32, vp, vp, vp, vp]
         L.laim_decode_bitcentric_form.argtypes = [vp, C.c_double, vp, i32, i32, i32, vp, vp, vp, vp]
         L.laim_resident_variant.argtypes = [vp, C.POINTER(Params), vp, i32p, i32p, i32p, i32p]
+        L.laim_launch_shape.argtypes = [vp, C.POINTER(Params), C.POINTER(ResidentCfg), i32, i32,
+                                        C.POINTER(LaunchInfo)]
         L.laim_decode_rounds_static.argtypes = [vp, C.POINTER(Params), vp, u64, i32, vp, vp, vp, vp,
                                                 vp, vp, i32, vp]
         L.laim_online_plan_create.argtypes = [vp, C.POINTER(OnlineParamsC), C.POINTER(vp)]
@@ -310,6 +318,21 @@ class Code:
                                           *[C.byref(o) for o in out]), "laim_resident_variant")
         return {"dc": out[0].value, "dv": out[1].value, "checks_per_thread": out[2].value,
                 "tiled": bool(out[3].value)}
+
+    def launch_shape(self, params: "DecodeParams", nshots: int, form: str = "auto", cfg: dict | None = None) -> dict:
+        """``laim_launch_shape``: the form a decode of ``nshots`` shots runs
+        ("resident", "stream" or "wide") and the resident form's shape."""
+        c = None
+        if cfg is not None:
+            c = ResidentCfg(cfg.get("threads_per_shot", 0), cfg.get("checks_per_thread", 0),
+                            cfg.get("shots_per_block", 0))
+        P, o = params.c(), LaunchInfo()
+        check(lib().laim_launch_shape(self.handle, C.byref(P), C.byref(c) if c is not None else None, nshots,
+                                      FORMS[form], C.byref(o)), "laim_launch_shape")
+        d = {f[0]: getattr(o, f[0]) for f in LaunchInfo._fields_}
+        d["form"] = {FORM_RESIDENT: "resident", FORM_STREAM: "stream", FORM_WIDE: "wide"}[o.form]
+        d["tiled"] = bool(o.tiled)
+        return d
 
     def set_resident_cfg(self, bp: str, cfg: dict | None):
         c = None
