@@ -269,7 +269,7 @@ __device__ __forceinline__ float boxplus1(float a, float b) {
 // 3 (D - 2) box-plus steps in D - 2 stages of independent ones: stage S forms
 // F_S, B_{D-1-S} and the outputs whose two folds the stages before it made
 // (output j in stage max(j - 1, D - 2 - j) + 1: none, one or two a stage).
-// LEAN: at most two steps at a time, for kernels short of registers.
+// LEAN: one step at a time, for kernels short of registers.
 template <int D, bool FAR, int S, bool LEAN>
 __device__ __forceinline__ void boxplus_stage(const float* x, float* F, float* B, float* acc) {
   if constexpr (S <= D - 2) {
@@ -289,10 +289,12 @@ __device__ __forceinline__ void boxplus_stage(const float* x, float* F, float* B
       a[3] = F[lo - 1];
       b[3] = B[lo + 1];
     }
-    if constexpr (LEAN && N > 2) {
-      boxplus<FAR, 2>(a, b, o);
-      __builtin_amdgcn_sched_barrier(0);
-      boxplus<FAR, N - 2>(a + 2, b + 2, o + 2);
+    if constexpr (LEAN) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        boxplus<FAR, 1>(a + i, b + i, o + i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     } else {
       boxplus<FAR, N>(a, b, o);
     }
