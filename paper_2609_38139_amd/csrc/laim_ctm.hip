@@ -30,6 +30,7 @@
 // registers at every turn, 70 scalar spills), 41.6 ms with the loop by
 // itself, 37.2 ms with two copies.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "device_math.h"
@@ -58,6 +59,14 @@ struct CtmKernArgs {
   CtmParamsDev P;
   CtmArgs a;
 };
+// The launch lays the three arguments out one after another, each at its own
+// alignment; these are 8-byte aligned and leave no gap.
+static_assert(alignof(DevCode) == 8 && alignof(CtmParamsDev) == 8 && alignof(CtmArgs) == 8,
+              "kernel arguments of 8-byte alignment");
+static_assert(offsetof(CtmKernArgs, P) == sizeof(DevCode) &&
+                  offsetof(CtmKernArgs, a) == sizeof(DevCode) + sizeof(CtmParamsDev) &&
+                  sizeof(CtmKernArgs) == sizeof(DevCode) + sizeof(CtmParamsDev) + sizeof(CtmArgs),
+              "the kernel's arguments as the launch lays them out");
 typedef const __attribute__((address_space(4))) CtmKernArgs* CtmArgPtr;
 __device__ __forceinline__ const CtmKernArgs& fresh(CtmArgPtr p) {
   asm volatile("" : "+s"(p));
