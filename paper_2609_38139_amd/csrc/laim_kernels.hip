@@ -1436,9 +1436,12 @@ __global__ void __launch_bounds__(1024) server_kernel(const BatchItemDev* items,
   // cost 3.4 us of a 100 us step each, and as much again between kernels);
   // the block reads its own requests from there once, in one round trip.
   {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(reqs_host + U.first);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(reqs + U.first);
-    for (int32_t i = tid_x(); i < U.count * (int32_t)(sizeof(ServerReqDev) / 4); i += bdim_x()) dst[i] = src[i];
+    typedef uint64_t __attribute__((may_alias)) Word;  // of a record's fields, whatever their type
+    static_assert(sizeof(ServerReqDev) % sizeof(Word) == 0 && alignof(ServerReqDev) == alignof(Word), "whole words");
+    const Word* src = reinterpret_cast<const Word*>(reqs_host + U.first);
+    Word* dst = reinterpret_cast<Word*>(reqs + U.first);
+    constexpr int32_t kWords = sizeof(ServerReqDev) / sizeof(Word);
+    for (int32_t i = tid_x(); i < U.count * kWords; i += bdim_x()) dst[i] = src[i];
   }
   __syncthreads();
   const BatchItemDev* I = items + U.item;
