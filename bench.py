@@ -60,6 +60,9 @@ BITCENTRIC_SOURCES = ("paper_2609_38139_amd/csrc/laim_bitcentric.hip", "paper_26
                       "paper_2609_38139_amd/csrc/laim_internal.h", "paper_2609_38139_amd/build.py")
 
 
+LINE_LIMIT = 8000  # characters of the benchmark's one line
+
+
 def profile_fields(profile: str, sources):
     """The machine-readable fields of a committed rocprofv3 summary, or None
     when the kernel sources (hashed in order) differ from the profiled ones."""
@@ -833,6 +836,19 @@ def cpu_baseline(args, spec, P_or, seconds, nthreads=None, max_shots=4096):
     return done, el, nthreads, rounds
 
 
+def emit(line, extras):
+    """The secondary measurements on stderr, one JSON line each, then the one
+    JSON line of the benchmark on stdout. That line stays short, so that a
+    reader who keeps the end of the output has all of it: with every secondary
+    measurement inside it had grown past 12,000 characters."""
+    for name, value in extras.items():
+        print("[bench] " + json.dumps({name: value}), file=sys.stderr, flush=True)
+    text = json.dumps(line)
+    if len(text) > LINE_LIMIT:
+        print(f"[bench] the line below has {len(text)} characters", file=sys.stderr, flush=True)
+    print(text, flush=True)
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -1084,13 +1100,13 @@ def main():
             if "serving" in extras else None),
         "roofline": rl,
         "cpu_baseline": cpu,
-        "extras": dict(extras, sweeps_not_computed={
-            "msg_updates_of_the_method_per_s": msg_method / sec,
-            "what": "the method's count: every sweep of every round run, including the identity sweeps "
-                    "at a fixed point that the kernel skips (not computed; msg_updates_per_s counts the "
-                    "computed ones)", "sweeps_computed_frac": round(sweeps_frac, 4)}),
     }
-    print(json.dumps(line), flush=True)
+    extras["sweeps_not_computed"] = {
+        "msg_updates_of_the_method_per_s": msg_method / sec,
+        "what": "the method's count: every sweep of every round run, including the identity sweeps "
+                "at a fixed point that the kernel skips (not computed; msg_updates_per_s counts the "
+                "computed ones)", "sweeps_computed_frac": round(sweeps_frac, 4)}
+    emit(line, extras)
     return 0
 
 
