@@ -332,8 +332,8 @@ laim_status laim_launch_shape(const laim_code* code, const laim_decode_params* p
  * batch that fills the device: min-sum on the 2D toric layout takes the tiled
  * variant (8 checks per thread, m / 8 threads per shot, blocks near 128 threads
  * with wavefronts at least 80% full); other min-sum decodes take 1 to 8 checks
- * per thread by the code's degrees, sum-product the fewest with at most 640
- * threads per shot, in blocks of at most 256 threads (or one shot) with their
+ * per thread by the code's degrees and size, sum-product the fewest with at most
+ * 640 threads per shot, in blocks of at most 256 threads (or one shot) with their
  * wavefronts full. Smaller batches take the fewest checks per thread whose
  * wavefronts the device holds at once. A field given as 0 in cfg is chosen by
  * the same rule, among the shapes whose block (threads_per_shot *

@@ -1473,6 +1473,10 @@ struct ResVariant {
   {DC, DV, CPT, 0, 0, 0, resident_kernel<DC, DV, CPT, 0, false>},                \
       {DC, DV, CPT, 1, 0, 0, resident_kernel<DC, DV, CPT, 1, false>}
 
+// The rule takes pairs with one check each; those with 2 and 4 run where a caller
+// or the autotuner asks for them (the fastest of all shapes in 8 of 234 cells of 27
+// codes, 16 to 65,536 shots: membrane L = 3 and 4 in large batches at low noise, by
+// up to 5%).
 #define LAIM_RES_PAIR(DC, DV, CPT) {DC, DV, CPT, 1, 1, 0, resident_pair_kernel<DC, DV, CPT>, 2}
 
 static const ResVariant kResVariants[] = {
@@ -1563,7 +1567,9 @@ static bool few_waves(int64_t nshots, int th, int per_simd, int cus) {
 //    holds many shots that wait for the slowest (2D toric L = 21, 16,384 shots 1.54
 //    / 0.91 / 0.82 / 0.82); the tiled variant always 8.
 //    (2, 2): up to 4 with at least 24 threads (repetition d = 101, 131,072 shots
-//    1.56 / 0.70 / 0.71 / 0.86).
+//    1.56 / 0.70 / 0.71 / 0.86; 32,768 shots, the best shots per block of each, d = 47
+//    0.148 / 0.126 / 0.134 / 0.150, d = 81 0.223 / 0.181 / 0.185 / 0.267, d = 31, where 16
+//    threads are too few for the line, 0.129 / 0.130 / 0.121 / 0.228).
 //    (6, 2), padded or not: 2 with 40 threads, 4 with 100, or with 40 where 4 halve
 //    the wavefronts and leave 48 per SIMD (3D point, p = 0.02: L = 6, 216 checks,
 //    65,536 shots - / 2.46 / 2.27, 32,768 - / 1.37 / 1.33, 8,192 - / 0.56 / 0.67;
@@ -1634,10 +1640,15 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
 // Whether the built-in rule puts a check on two lanes, one check per pair
 // (sum-product): shorter chains per lane for the same work in all. It pays
 // while wavefronts are few -- up to 8 per SIMD counted at one lane per check, and
-// blocks of at most 900 threads, past which one block alone keeps every SIMD
-// busy (ms at one and two lanes: 2D toric L = 16, 16 / 1,024 / 4,096 shots
-// 0.28 / 0.58 / 1.69 and 0.23 / 0.54 / 1.81; 3D point L = 8, 512 checks, 256 shots
-// 0.99 and 1.11) -- and at any batch size on (6, 3) codes of at most 320 threads: a
+// blocks of at most 900 threads (us at one and two lanes, 32 rounds at the codes'
+// usual noise and 8 at a fifth of it: 3D point L = 7, 343 checks, 16 / 256 / 1,024
+// shots 265 / 407 / 1,048 and 243 / 372 / 946, at low noise 152 / 188 / 350 and 135 / 173 /
+// 363; 2D toric L = 18, 324 checks, 16 / 256 / 1,024 shots 157 / 696 / 853 and 135 / 640 /
+// 825, 84 / 153 / 261 and 74 / 135 / 279; (6, 3) of 378 checks 265 / 1,292 / 1,377 and 224 /
+// 1,096 / 1,231. It fades towards the block's limit: L = 20, 400 checks, 16 / 256 / 1,024
+// shots 704 / 703 / 896 and 675 / 766 / 1,098, 106 / 150 / 246 and 102 / 135 / 277; with 1,024
+// threads, 3D point L = 8, it loses at every size, 16 / 256 / 1,024 shots 548 / 634 /
+// 1,236 and 601 / 710 / 1,584) -- and at any batch size on (6, 3) codes of at most 320 threads: a
 // few shots that never clear set the end of a launch of their short shots (ms
 // at one and two lanes, 32,768 shots, p = 0.03, 32 rounds and p = 0.006, 8 rounds: 36
 // checks 0.57 / 0.52 and 0.25 / 0.22, 72 2.09 / 1.60 and 0.47 / 0.44, 144 3.35 / 3.11
