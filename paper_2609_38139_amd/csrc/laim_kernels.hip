@@ -1474,8 +1474,8 @@ struct ResVariant {
       {DC, DV, CPT, 1, 0, 0, resident_kernel<DC, DV, CPT, 1, false>}
 
 // The rule takes pairs with one check each; those with 2 and 4 run where a caller
-// or the autotuner asks for them (the fastest of all shapes in 8 of 234 cells of 27
-// codes, 16 to 65,536 shots: membrane L = 3 and 4 in large batches at low noise, by
+// or the autotuner asks for them (the fastest of all shapes in 8 of 234 cells of 24
+// codes, 1,024 to 65,536 shots: membrane L = 3 and 4 in large batches at low noise, by
 // up to 5%).
 #define LAIM_RES_PAIR(DC, DV, CPT) {DC, DV, CPT, 1, 1, 0, resident_pair_kernel<DC, DV, CPT>, 2}
 
