@@ -311,7 +311,8 @@ laim_status laim_resident_variant(const laim_code* code, const laim_decode_param
 
 /* laim_launch_shape -- what laim_decode_rounds in `form` (or, with cfg,
  * laim_decode_rounds_cfg) runs for these parameters and nshots shots. A plan
- * group, an online window and a server choose by the same rules. Errors: those
+ * group and an online window choose by the same rules (a server by those for
+ * few shots of many rounds). Errors: those
  * of the decode call for the same arguments. */
 #define LAIM_FORM_WIDE 3 /* reported only: AUTO's one block per shot for larger codes */
 typedef struct {
@@ -335,7 +336,8 @@ laim_status laim_launch_shape(const laim_code* code, const laim_decode_params* p
  * per thread by the code's degrees and size, sum-product the fewest with at most
  * 640 threads per shot, in blocks of at most 256 threads (or one shot) with their
  * wavefronts full. Smaller batches take the fewest checks per thread whose
- * wavefronts the device holds at once. A field given as 0 in cfg is chosen by
+ * wavefronts the device holds at once. Decodes of at most two rounds have lines of
+ * their own (more checks per thread, fuller blocks). A field given as 0 in cfg is chosen by
  * the same rule, among the shapes whose block (threads_per_shot *
  * shots_per_block) has at most 1024 threads; whether it runs does not depend on
  * the batch size. */

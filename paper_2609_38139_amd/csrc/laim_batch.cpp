@@ -153,7 +153,7 @@ laim_status laim_batch_plan_create(const laim_batch_item* items, int32_t nitems,
   for (Group& gr : groups) {
     const laim_resident_cfg* want = gr.code->has_cfg[gr.kp.bp] ? &gr.code->cfg[gr.kp.bp] : nullptr;
     if (!resident_shape(gr.code->dev, gr.kp.bp, want, &gr.sh, device, gr.kp.conflict == kConflictSequential,
-                        reg_dv2_ok(gr.kp), gr.total))
+                        reg_dv2_ok(gr.kp), gr.total, brief_rounds(gr.kp)))
       return LAIM_EUNSUP;  // (not reached: the same code fitted above)
   }
   // the largest groups first

@@ -615,11 +615,11 @@ laim_status laim_logical_failure(const laim_code* code, const uint8_t* e0, const
   return er == hipSuccess ? LAIM_OK : hip_fail(er, "failure kernel");
 }
 
-static int resolve_form(const laim_code* code, int bp, bool seq, bool reg2, int form, int64_t nshots,
-                        ResidentShape* sh) {
-  const laim_resident_cfg* want = code->has_cfg[bp] ? &code->cfg[bp] : nullptr;
+static int resolve_form(const laim_code* code, const KParams& kp, int form, int64_t nshots, ResidentShape* sh) {
+  const laim_resident_cfg* want = code->has_cfg[kp.bp] ? &code->cfg[kp.bp] : nullptr;
   if (form == LAIM_FORM_STREAM) return LAIM_FORM_STREAM;
-  const bool ok = resident_shape(code->dev, bp, want, sh, code->device, seq, reg2, nshots);
+  const bool ok = resident_shape(code->dev, kp.bp, want, sh, code->device, kp.conflict == kConflictSequential,
+                                 reg_dv2_ok(kp), nshots, brief_rounds(kp));
   if (form == LAIM_FORM_RESIDENT) return ok ? LAIM_FORM_RESIDENT : -1;
   return ok ? LAIM_FORM_RESIDENT : LAIM_FORM_STREAM;
 }
@@ -641,7 +641,8 @@ laim_status laim_resident_variant(const laim_code* code, const laim_decode_param
   const bool seq = kp.conflict == kConflictSequential;
   const laim_resident_cfg* want = cfg ? cfg : (code->has_cfg[kp.bp] ? &code->cfg[kp.bp] : nullptr);
   ResidentShape sh;
-  if (!resident_shape(code->dev, kp.bp, want, &sh, code->device, seq, reg_dv2_ok(kp))) return LAIM_EUNSUP;
+  if (!resident_shape(code->dev, kp.bp, want, &sh, code->device, seq, reg_dv2_ok(kp), 0, brief_rounds(kp)))
+    return LAIM_EUNSUP;
   if (dc) *dc = sh.dc;
   if (dv) *dv = sh.dv;
   if (checks_per_thread) *checks_per_thread = sh.cpt;
@@ -656,7 +657,7 @@ size_t laim_workspace_bytes(const laim_code* code, const laim_decode_params* par
   const bool seq = params->conflict == LAIM_CONFLICT_SEQUENTIAL;
   KParams kp;
   if (resolve_params(params, &kp) != LAIM_OK) return 0;
-  int f = resolve_form(code, kp.bp, seq, reg_dv2_ok(kp), form, nshots, &sh);
+  int f = resolve_form(code, kp, form, nshots, &sh);
   if (params->bp == 0 && params->alpha > 1.0f) f = (form == LAIM_FORM_RESIDENT) ? -1 : LAIM_FORM_STREAM;
   if (f == LAIM_FORM_RESIDENT) return resident_workspace_bytes();
   if (f == LAIM_FORM_STREAM) return stream_workspace_bytes(code->dev, nshots, seq);
@@ -671,7 +672,6 @@ namespace laim {
 // resident one, its shape.
 static laim_status choose_form(const laim_code* code, const KParams& kp, int32_t nshots, int32_t form,
                                const laim_resident_cfg* cfg, ResidentShape* sh, int* f) {
-  const bool seq = kp.conflict == kConflictSequential;
   // The resident min-sum kernel relies on alpha <= 1 (its outputs cannot
   // reach the clamp); other scales run in the stream form.
   const bool resident_ok = !(kp.bp == 0 && kp.alpha > 1.0f);
@@ -680,7 +680,9 @@ static laim_status choose_form(const laim_code* code, const KParams& kp, int32_t
       set_error("the resident min-sum form needs alpha <= 1");
       return LAIM_EUNSUP;
     }
-    if (!resident_shape(code->dev, kp.bp, cfg, sh, code->device, seq, reg_dv2_ok(kp), nshots)) return LAIM_EINVAL;
+    if (!resident_shape(code->dev, kp.bp, cfg, sh, code->device, kp.conflict == kConflictSequential, reg_dv2_ok(kp),
+                        nshots, brief_rounds(kp)))
+      return LAIM_EINVAL;
     *f = LAIM_FORM_RESIDENT;
   } else if (!resident_ok) {
     if (form == LAIM_FORM_RESIDENT) {
@@ -689,7 +691,7 @@ static laim_status choose_form(const laim_code* code, const KParams& kp, int32_t
     }
     *f = LAIM_FORM_STREAM;
   } else {
-    *f = resolve_form(code, kp.bp, seq, reg_dv2_ok(kp), form, nshots, sh);
+    *f = resolve_form(code, kp, form, nshots, sh);
     if (*f < 0) {
       set_error("the code cannot run in the resident form (a shot's state exceeds the LDS or its "
                 "degrees have no compiled variant)");

@@ -116,9 +116,11 @@ inline bool reg_dv2_ok(const KParams& kp) {
 // error text) if the code cannot run resident with it. With reg2 false the
 // exact variants for qubit degree 2 are not used (the padded one is). nshots:
 // the shots of the launch, or 0 for the shape of a batch that fills the device
-// (whether a code can run does not depend on it).
+// (whether a code can run does not depend on it). brief: a decode of few rounds
+// (brief_rounds), whose shots end together (nor on this).
 bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, ResidentShape* out,
-                    int device, bool seq = false, bool reg2 = true, int64_t nshots = 0);
+                    int device, bool seq = false, bool reg2 = true, int64_t nshots = 0, bool brief = false);
+inline bool brief_rounds(const KParams& kp) { return kp.rounds <= 2; }
 size_t resident_workspace_bytes();
 // sweeps[i] = iters x (rounds shot i ran), for the forms that run every sweep
 hipError_t launch_sweep_count(const KParams& kp, const int32_t* tclr, int32_t nshots, int32_t* sweeps,

@@ -1591,6 +1591,18 @@ static bool few_waves(int64_t nshots, int th, int per_simd, int cus) {
 //    toric L = 32, 16,384 shots 23.8 / 21.9 / 23.4 / 30.5; 3D point L = 12, 4,096
 //    shots - / 36.9 / 34.0 / 39.4); checks of degree 2 have no box-plus step
 //    and follow the min-sum rule.
+//  - A decode of at most two rounds (brief), whose shots end together: nothing waits
+//    for a slow shot, and fewer, fuller wavefronts do better on a full device (us, one
+//    round). Min-sum on (6, 2) codes takes 4 with 40 threads (3D point at 2 / 4: L = 6, 4,096 shots 70 / 51, 32,768 383 / 340; L = 7
+//    576 / 503 and, 8,192, 171 / 157). Sum-product starts at 2 checks per thread above 128 checks (qubit degree
+//    2; 256 above that) and 4 above 512 (8,192 shots at 1 / 2 / 4: 2D toric L = 18,
+//    324 checks, 580 / 464 / 487; L = 24, 576, 1,158 / 949 / 835; 3D point L = 5, 125, 271
+//    / 282 / 286; L = 6, 216, 4,096 shots 270 / 270 / 283; (6, 3), 180 checks, 316 /
+//    338 / 384; membrane L = 4, 192, 184 / 175 / 204). Min-sum on (4, 4) and (6, 3) codes of
+//    more than 512 checks takes 4 if they leave more than 16 wavefronts per SIMD ((6, 3) of
+//    900 checks at 1 / 2 / 4, 8,192 shots 738 / 520 / 468, 4,096, 16 per SIMD, 375 / 267 /
+//    267; membrane L = 6, 648 checks, 300 / 340 / 292 and, 12 per SIMD, 160 / 179 /
+//    173).
 //  - Otherwise the fewest whose wavefronts number at most 4 per SIMD: few_waves
 //    (2D toric L = 16, min-sum, 1,024 shots, 4 per SIMD at one check per thread:
 //    0.090 ms against 0.205 with the tiled variant; 4,096 shots, 4 per SIMD at
@@ -1602,7 +1614,7 @@ static bool few_waves(int64_t nshots, int th, int per_simd, int cus) {
 // alike, so that whether a shape is accepted does not depend on nshots.
 constexpr int kMaxBlock = 1024;
 static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool tile_ok, int64_t nshots, int cus,
-                        int spb) {
+                        int spb, bool brief) {
   auto threads = [&](int cpt) { return (c.m + cpt - 1) / cpt; };
   auto usable = [&](int cpt) {
     return threads(cpt) * std::max(spb, 1) <= kMaxBlock && find_variant(dc, dv, cpt, bp, reg);
@@ -1610,22 +1622,25 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
   static const int order[] = {1, 2, 4, 8};
   int full = 0;
   if (bp != 0 && dc > 2) {
+    const int start = !brief || c.m <= (dv == 2 ? 128 : 256) ? 1 : c.m <= 512 ? 2 : 4;
     for (int a : order)
-      if (!full && usable(a) && threads(a) <= 640) full = a;
+      if (!full && a >= start && usable(a) && threads(a) <= 640) full = a;
   } else if (tile_ok) {
     full = 8;
   } else {
     auto waves = [&](int a) { return (threads(a) + 63) / 64; };
     auto halves = [&](int a) { return 2 * waves(a) <= waves(a / 2); };
+    const bool four = brief && c.m > 512 && !few_waves(nshots, 64 * waves(4), 16, cus);
     auto pays = [&](int a) {
       if (dc == 2) return a <= 4 && threads(a) >= 24;
       if (dc == 4 && dv == 2) return threads(a) >= 40;
       if (dv == 2)
-        return a <= 4 && (threads(a) >= (a == 4 ? 100 : 40) ||
+        return a <= 4 && (threads(a) >= (a == 4 && !brief ? 100 : 40) ||
                           (threads(a) >= 40 && halves(a) && !few_waves(nshots, 64 * waves(a), 48, cus)));
       if (dc == 4)
-        return a == 2 && c.m > 256 && c.m <= 512 && halves(a) && !few_waves(nshots, 64 * waves(1), 31, cus);
-      return a == 2 && c.m > 256;
+        return (a == 2 && c.m > 256 && c.m <= 512 && halves(a) && !few_waves(nshots, 64 * waves(1), 31, cus)) ||
+               (a == 4 && four);
+      return (a == 2 && c.m > 256) || (a == 4 && four);
     };
     for (int a : order)
       if (usable(a) && (!full || pays(a))) full = a;
@@ -1653,10 +1668,17 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
 // at one and two lanes, 32,768 shots, p = 0.03, 32 rounds and p = 0.006, 8 rounds: 36
 // checks 0.57 / 0.52 and 0.25 / 0.22, 72 2.09 / 1.60 and 0.47 / 0.44, 144 3.35 / 3.11
 // and 1.13 / 1.15; 180 checks 3.68 / 4.42 and 1.15 / 1.67, 288 7.96 / 9.94 and 2.98 /
-// 4.08, 432 9.64 / 13.8 and 3.92 / 5.92).
-static bool pairs_pay(const DevCode& c, int bp, int dc, int dv, int reg, int64_t nshots, int cus, int spb) {
+// 4.08, 432 9.64 / 13.8 and 3.92 / 5.92). A decode of at most two rounds, whose shots
+// all run as long, has no such end: up to 2 wavefronts per SIMD (one round, us at one and
+// two lanes: 2D toric L = 8, 64 checks, 1,024 shots 27 / 21, 4,096, 4 per SIMD, 49 / 93,
+// 8,192 82 / 139; (6, 3), 72 checks, 1,024 shots, 2 per SIMD, 46 / 36, 8,192 162 / 185; 180
+// checks, 1,024 shots, 3 per SIMD, 64 / 83; 3D point L = 5, 125 checks, 1,024 shots, 2 per
+// SIMD, 51 / 51, 4,096 144 / 177).
+static bool pairs_pay(const DevCode& c, int bp, int dc, int dv, int reg, int64_t nshots, int cus, int spb,
+                      bool brief) {
   if (bp != 1 || 2 * c.m > 900 || 2 * c.m * std::max(spb, 1) > kMaxBlock || !find_variant(dc, dv, 1, bp, reg, 0, 2))
     return false;
+  if (brief) return few_waves(nshots, c.m, 2, cus);
   return (dv == 3 && 2 * c.m <= 320) || (nshots > 0 && nshots * ((c.m + 63) / 64) <= (int64_t)8 * 4 * cus);
 }
 
@@ -1680,7 +1702,7 @@ static int built_in_spb(int nt, int least) {
 }
 
 bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, ResidentShape* out,
-                    int device, bool seq, bool reg2, int64_t nshots) {
+                    int device, bool seq, bool reg2, int64_t nshots, bool brief) {
   int dc, dv, reg;
   if (!pick_degrees(c, reg2, &dc, &dv, &reg)) {
     set_error("resident form needs check degree <= 8 and qubit degree <= 4 (have %d, %d)", c.dcmax,
@@ -1699,10 +1721,11 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
   // than the other shapes at every L measured (8 to 64)
   const bool tile_ok = c.tile_chk && bp == 0 && dc == 4 && dv == 2 && reg && !seq;
   const int cus = device_cus(device);
+  brief = brief && reg;  // (the lines for brief decodes were drawn on the exact variants)
   int lpc = 1;
   if (cpt <= 0 && nt <= 0) {
-    cpt = built_in_cpt(c, bp, dc, dv, reg, tile_ok, nshots, cus, spb);
-    if (pairs_pay(c, bp, dc, dv, reg, nshots, cus, spb)) {
+    cpt = built_in_cpt(c, bp, dc, dv, reg, tile_ok, nshots, cus, spb, brief);
+    if (pairs_pay(c, bp, dc, dv, reg, nshots, cus, spb, brief)) {
       cpt = 1;
       lpc = 2;
     }
@@ -1739,12 +1762,13 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
   if (spb <= 0 && tile_ok && cpt == 8 && nt * 8 == c.m) {
     // one wavefront, whose barriers cost nothing, if two shots or more fill 80%
     // of it (65,536 shots, ms with one wavefront and with about 128 threads: L = 8
-    // 0.463 / 0.477, L = 12 0.85 / 1.01, L = 16 1.25 / 1.36); else blocks near 128
-    // threads with wavefronts at least 80% full (128 threads best at L = 32, 216 at
-    // L = 24)
+    // 0.463 / 0.477, L = 12 0.85 / 1.01, L = 16 1.25 / 1.36); else, and where a decode of at
+    // most two rounds claims its next shots sooner (one round, L = 8, 65,536 shots 0.182 /
+    // 0.146; L = 16, 16,384 shots 0.188 / 0.148), blocks near 128 threads with wavefronts
+    // at least 80% full (128 threads best at L = 32, 216 at L = 24)
     int best = 0, gap = 0;
     const int one = 64 / nt;  // shots of one wavefront
-    const bool single = one >= 2 && 5 * nt * one >= 4 * 64;
+    const bool single = !brief && one >= 2 && 5 * nt * one >= 4 * 64;
     if (single) best = one;
     for (int s = 1; !single && nt * s <= kTileMaxThreads; ++s) {
       const int th = nt * s, waves = (th + 63) / 64;
@@ -1769,8 +1793,17 @@ bool resident_shape(const DevCode& c, int bp, const laim_resident_cfg* want, Res
     // threads, 5 and 10 141 / 142 and 133 / 104; L = 11, 61 threads, 1 and 2 486 / 399
     // and 458 / 255. More do not pay: 3D point L = 5, 63 threads, 750 messages, 1 and 2
     // 659 / 745 and 465 / 282.)
+    // A decode of at most two rounds claims its next shots sooner, and its shots end
+    // together: blocks near 256 threads, for both rules, with more than 5 wavefronts per
+    // SIMD (one round, 8,192 shots, us with fewer and so: min-sum, 2D toric L = 9, 41
+    // threads, 3 and 6 a block 78 / 51; L = 10, 50 threads, 1 and 5 159 / 55; 3D point L = 5,
+    // 63 threads, 1 and 4 160 / 72; sum-product, 2D toric L = 9, 81 threads, 1 and 3 182 /
+    // 123; 3D point L = 5, 125 threads, 1 and 2 296 / 271. With 3 per SIMD, L = 9, 4,096
+    // shots, min-sum, 1 and 6 23 / 24).
     int64_t least = 1;
-    if ((bp == 0 || dc == 2) && lpc == 1 && !few_waves(nshots, nt, 6, cus)) {
+    if (brief && lpc == 1) {
+      if (!few_waves(nshots, nt, 5, cus)) least = std::max(1, 256 / nt);
+    } else if ((bp == 0 || dc == 2) && lpc == 1 && !few_waves(nshots, nt, 6, cus)) {
       least = (576 + c.m * dc - 1) / (c.m * dc);
       const int64_t room = nshots / (8 * (int64_t)cus);  // 0 shots: a full device
       if (nshots > 0 && least > room) least = std::max<int64_t>(room, 1);

@@ -210,7 +210,7 @@ size_t window_decode_bytes(const laim_code* wc, const KParams& kp, int32_t nshot
   const bool seq = kp.conflict == kConflictSequential;
   const laim_resident_cfg* want = wc->has_cfg[kp.bp] ? &wc->cfg[kp.bp] : nullptr;
   *resident = !(kp.bp == 0 && kp.alpha > 1.0f) &&
-              resident_shape(wc->dev, kp.bp, want, sh, wc->device, seq, reg_dv2_ok(kp), nshots);
+              resident_shape(wc->dev, kp.bp, want, sh, wc->device, seq, reg_dv2_ok(kp), nshots, brief_rounds(kp));
   return *resident ? resident_workspace_bytes() : stream_workspace_bytes(wc->dev, nshots, seq);
 }
 

@@ -3,7 +3,7 @@
 // only (without a device the library assumes 64 KiB of LDS and 256 compute units). Test
 // infrastructure.
 //
-// stdin: lines "m n dc dv regular lattice bp seq spb nshots"; stdout: per line
+// stdin: lines "m n dc dv regular lattice bp seq spb nshots brief"; stdout: per line
 // "accepted-in-full accepted threads checks lanes shots"
 #include <cstdio>
 
@@ -12,11 +12,11 @@
 using namespace laim;
 
 int main() {
-  int m, n, dc, dv, regular, lattice, bp, seq, spb;
+  int m, n, dc, dv, regular, lattice, bp, seq, spb, brief;
   long long nshots;
   static const int32_t table = 0;
-  while (std::scanf("%d %d %d %d %d %d %d %d %d %lld", &m, &n, &dc, &dv, &regular, &lattice, &bp, &seq, &spb,
-                    &nshots) == 10) {
+  while (std::scanf("%d %d %d %d %d %d %d %d %d %lld %d", &m, &n, &dc, &dv, &regular, &lattice, &bp, &seq, &spb,
+                    &nshots, &brief) == 11) {
     DevCode c = {};
     c.m = m;
     c.n = n;
@@ -26,7 +26,7 @@ int main() {
     c.tile_chk = lattice ? &table : nullptr;  // (its presence alone decides)
     ResidentShape sh;
     auto runs = [&](const laim_resident_cfg& cfg, long long shots) {
-      return resident_shape(c, bp, &cfg, &sh, 0, seq != 0, true, shots);
+      return resident_shape(c, bp, &cfg, &sh, 0, seq != 0, true, shots, brief != 0);
     };
     // In full: one check per thread up to 256 checks, two up to 512, four up to 1024 (eight on the 2D
     // toric lattice with min-sum), the next compiled number above, else the largest compiled.

@@ -53,14 +53,15 @@ def test_a_shape_with_shots_per_block_alone_is_accepted_at_every_batch_size(shap
             for bp in (0, 1):
                 for seq in (0, 1):
                     for spb in (1, 2, 3, 4, 5, 8, 13, 16, 31, 40):
-                        rows += [(m, m * per, dc, dv, regular, lattice, bp, seq, spb, n) for n in BATCHES]
+                        rows += [(m, m * per, dc, dv, regular, lattice, bp, seq, spb, n, brief)
+                                 for n in BATCHES for brief in (0, 1)]
     got = shapes(rows)
     assert len(got) == len(rows)
     accepted = 0
-    for i in range(0, len(rows), len(BATCHES)):
-        row, outs = rows[i], got[i:i + len(BATCHES)]
+    for i in range(0, len(rows), 2 * len(BATCHES)):
+        row, outs = rows[i], got[i:i + 2 * len(BATCHES)]
         oks = {o[1] for o in outs}
-        assert len(oks) == 1, (row, outs)  # the answer does not depend on the batch
+        assert len(oks) == 1, (row, outs)  # the answer depends neither on the batch nor on the rounds
         if outs[0][0]:  # and is yes wherever the block written out in full runs
             assert oks == {1}, (row, outs)
         for _, ok, nt, cpt, lanes, spb in outs:
@@ -70,9 +71,9 @@ def test_a_shape_with_shots_per_block_alone_is_accepted_at_every_batch_size(shap
     assert accepted > 10000
 
 
-def shape_of(shapes, m, dc, dv, regular, bp, nshots, per=2):
+def shape_of(shapes, m, dc, dv, regular, bp, nshots, per=2, brief=0):
     """(threads, checks per thread, lanes per check, shots per block) of the rule's own choice."""
-    (_, ok, *shape), = shapes([(m, m * per, dc, dv, regular, 0, bp, 0, 0, nshots)])
+    (_, ok, *shape), = shapes([(m, m * per, dc, dv, regular, 0, bp, 0, 0, nshots, brief)])
     assert ok
     return tuple(shape)
 
@@ -113,6 +114,21 @@ def test_two_lanes_per_check_on_6_3_codes(shapes, m, nshots, lanes):
     (4, 4, 375, 5290, 1), (4, 4, 375, 5500, 2), (4, 4, 375, 1024, 1)])
 def test_checks_per_thread_by_the_wavefronts_in_flight(shapes, dc, dv, m, nshots, cpt):
     assert shape_of(shapes, m, dc, dv, 1, 0, nshots, per=1)[1] == cpt
+
+
+@pytest.mark.parametrize("dc,dv,m,bp,nshots,shape", [
+    (4, 2, 64, 1, 2048, (128, 1, 2, 1)), (4, 2, 64, 1, 2049, (64, 1, 1, 1)), (4, 2, 64, 1, 8192, (64, 1, 1, 4)),
+    (6, 3, 72, 1, 1024, (144, 1, 2, 1)), (6, 3, 72, 1, 1025, (72, 1, 1, 3)), (6, 3, 72, 1, 0, (72, 1, 1, 3)),
+    (4, 2, 128, 1, 0, (128, 1, 1, 2)), (4, 2, 129, 1, 0, (65, 2, 1, 3)), (4, 2, 512, 1, 0, (256, 2, 1, 1)),
+    (4, 2, 513, 1, 0, (129, 4, 1, 1)), (6, 3, 256, 1, 0, (256, 1, 1, 1)), (6, 3, 257, 1, 0, (129, 2, 1, 1)),
+    (4, 4, 192, 1, 8192, (192, 1, 1, 1)), (4, 4, 648, 0, 5461, (648, 1, 1, 1)), (4, 4, 648, 0, 5462, (162, 4, 1, 1)),
+    (4, 4, 512, 0, 0, (256, 2, 1, 1)), (6, 3, 900, 0, 4096, (450, 2, 1, 1)), (6, 3, 900, 0, 4097, (225, 4, 1, 1)),
+    (4, 2, 81, 0, 7992, (41, 2, 1, 3)), (4, 2, 81, 0, 7993, (41, 2, 1, 6)), (6, 2, 125, 0, 8192, (63, 2, 1, 4)),
+    (6, 2, 216, 0, 4096, (54, 4, 1, 1)), (6, 2, 216, 0, 8192, (54, 4, 1, 4)), (6, 2, 343, 0, 0, (86, 4, 1, 2)),
+    (6, 2, 125, 0, 0, (63, 2, 1, 4)),
+    (8, 4, 900, 0, 0, (450, 2, 1, 1))])
+def test_decodes_of_at_most_two_rounds(shapes, dc, dv, m, bp, nshots, shape):
+    assert shape_of(shapes, m, dc, dv, int(dc != 8), bp, nshots, per=1, brief=1) == shape
 
 
 def test_wide_form_by_messages_and_shots(wide):
