@@ -1589,20 +1589,27 @@ static bool few_waves(int64_t nshots, int th, int per_simd, int cus) {
 //    448 1.32 / 1.26 / 4.72, 900 3.69 / 3.02 / 10.3).
 //  - Full device, sum-product: the fewest with at most 640 threads per shot (2D
 //    toric L = 32, 16,384 shots 23.8 / 21.9 / 23.4 / 30.5; 3D point L = 12, 4,096
-//    shots - / 36.9 / 34.0 / 39.4); checks of degree 2 have no box-plus step
-//    and follow the min-sum rule.
+//    shots - / 36.9 / 34.0 / 39.4); on (4, 2) codes 2 above 512 checks if 1 would make
+//    more than 31 wavefronts per SIMD, and on 321 to 512 checks if they take half the
+//    wavefronts and 1 would make more than 47 (p = 0.05, 4 and 32 rounds, 16,384 shots at 1
+//    / 2: L = 17, 289 checks, 2.84 / 2.84 and 4.29 / 4.60; L = 18, 324, 3.69 / 2.88 and
+//    5.54 / 4.80, 2,048 shots 0.546 / 0.495 and 1.25 / 1.51; L = 21, 441 checks in 7 or 4
+//    wavefronts, 8,192 shots 2.03 / 1.83 and 3.44 / 3.77; L = 24, 576, 16,384 shots 7.94 /
+//    6.51 and 13.0 / 11.0, 4,096 2.05 / 1.74 and 3.79 / 3.48); checks of degree 2 have no
+//    box-plus step and follow the min-sum rule.
 //  - A decode of at most two rounds (brief), whose shots end together: nothing waits
 //    for a slow shot, and fewer, fuller wavefronts do better on a full device (us, one
-//    round). Min-sum on (6, 2) codes takes 4 with 40 threads (3D point at 2 / 4: L = 6, 4,096 shots 70 / 51, 32,768 383 / 340; L = 7
-//    576 / 503 and, 8,192, 171 / 157). Sum-product starts at 2 checks per thread above 128 checks (qubit degree
-//    2; 256 above that) and 4 above 512 (8,192 shots at 1 / 2 / 4: 2D toric L = 18,
-//    324 checks, 580 / 464 / 487; L = 24, 576, 1,158 / 949 / 835; 3D point L = 5, 125, 271
+//    round). Min-sum on (6, 2) codes takes 4 with 40 threads (3D point at 2 / 4: L = 6,
+//    4,096 shots 70 / 51, 32,768 383 / 340; L = 7 576 / 503 and, 8,192, 171 / 157).
+//    Sum-product starts at 2 checks per thread above 128 checks (qubit degree 2; 256
+//    above that) and 4 above 512 (8,192 shots at 1 / 2 / 4: 2D toric L = 18, 324
+//    checks, 580 / 464 / 487; L = 24, 576, 1,158 / 949 / 835; 3D point L = 5, 125, 271
 //    / 282 / 286; L = 6, 216, 4,096 shots 270 / 270 / 283; (6, 3), 180 checks, 316 /
-//    338 / 384; membrane L = 4, 192, 184 / 175 / 204). Min-sum on (4, 4) and (6, 3) codes of
-//    more than 512 checks takes 4 if they leave more than 16 wavefronts per SIMD ((6, 3) of
-//    900 checks at 1 / 2 / 4, 8,192 shots 738 / 520 / 468, 4,096, 16 per SIMD, 375 / 267 /
-//    267; membrane L = 6, 648 checks, 300 / 340 / 292 and, 12 per SIMD, 160 / 179 /
-//    173).
+//    338 / 384; membrane L = 4, 192, 184 / 175 / 204). Min-sum on (4, 4) and (6, 3)
+//    codes of more than 512 checks takes 4 if they leave more than 16 wavefronts per
+//    SIMD ((6, 3) of 900 checks at 1 / 2 / 4, 8,192 shots 738 / 520 / 468, 4,096, 16
+//    per SIMD, 375 / 267 / 267; membrane L = 6, 648 checks, 300 / 340 / 292 and, 12 per
+//    SIMD, 160 / 179 / 173).
 //  - Otherwise the fewest whose wavefronts number at most 4 per SIMD: few_waves
 //    (2D toric L = 16, min-sum, 1,024 shots, 4 per SIMD at one check per thread:
 //    0.090 ms against 0.205 with the tiled variant; 4,096 shots, 4 per SIMD at
@@ -1616,20 +1623,24 @@ constexpr int kMaxBlock = 1024;
 static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool tile_ok, int64_t nshots, int cus,
                         int spb, bool brief) {
   auto threads = [&](int cpt) { return (c.m + cpt - 1) / cpt; };
+  auto waves = [&](int a) { return (threads(a) + 63) / 64; };
+  auto halves = [&](int a) { return 2 * waves(a) <= waves(a / 2); };
   auto usable = [&](int cpt) {
     return threads(cpt) * std::max(spb, 1) <= kMaxBlock && find_variant(dc, dv, cpt, bp, reg);
   };
   static const int order[] = {1, 2, 4, 8};
   int full = 0;
   if (bp != 0 && dc > 2) {
-    const int start = !brief || c.m <= (dv == 2 ? 128 : 256) ? 1 : c.m <= 512 ? 2 : 4;
+    int start = 1;
+    if (brief && c.m > (dv == 2 ? 128 : 256)) start = c.m <= 512 ? 2 : 4;
+    if (!brief && reg && dc == 4 && dv == 2 && c.m > 320 && (halves(2) || c.m > 512) &&
+        !few_waves(nshots, 64 * waves(1), c.m > 512 ? 31 : 47, cus))
+      start = 2;
     for (int a : order)
       if (!full && a >= start && usable(a) && threads(a) <= 640) full = a;
   } else if (tile_ok) {
     full = 8;
   } else {
-    auto waves = [&](int a) { return (threads(a) + 63) / 64; };
-    auto halves = [&](int a) { return 2 * waves(a) <= waves(a / 2); };
     const bool four = brief && c.m > 512 && !few_waves(nshots, 64 * waves(4), 16, cus);
     auto pays = [&](int a) {
       if (dc == 2) return a <= 4 && threads(a) >= 24;

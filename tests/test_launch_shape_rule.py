@@ -131,6 +131,13 @@ def test_decodes_of_at_most_two_rounds(shapes, dc, dv, m, bp, nshots, shape):
     assert shape_of(shapes, m, dc, dv, int(dc != 8), bp, nshots, per=1, brief=1) == shape
 
 
+@pytest.mark.parametrize("m,nshots,cpt", [(320, 0, 1), (324, 0, 2), (324, 8192, 2), (324, 8022, 2), (324, 8021, 1),
+                                          (484, 6016, 1), (400, 8192, 1), (512, 8192, 2), (513, 8192, 2),
+                                          (576, 8192, 2), (576, 3527, 1), (576, 3528, 2), (1024, 8192, 2)])
+def test_sum_product_checks_per_thread_on_4_2_codes(shapes, m, nshots, cpt):
+    assert shape_of(shapes, m, 4, 2, 1, 1, nshots)[1:3] == (cpt, 1)
+
+
 def test_wide_form_by_messages_and_shots(wide):
     rows = [((4900, 9800, 4, 2), 1, 1), ((22500, 45000, 4, 2), 1, 1), ((25600, 51200, 4, 2), 1, 0),
             ((32400, 64800, 4, 2), 1, 0), ((13824, 41472, 6, 2), 1, 1), ((17576, 52728, 6, 2), 1, 0),
