@@ -1664,32 +1664,35 @@ static int built_in_cpt(const DevCode& c, int bp, int dc, int dv, int reg, bool 
 }
 
 // Whether the built-in rule puts a check on two lanes, one check per pair
-// (sum-product): shorter chains per lane for the same work in all. It pays
-// while wavefronts are few -- up to 8 per SIMD counted at one lane per check, and
-// blocks of at most 900 threads (us at one and two lanes, 32 rounds at the codes'
-// usual noise and 8 at a fifth of it: 3D point L = 7, 343 checks, 16 / 256 / 1,024
-// shots 265 / 407 / 1,048 and 243 / 372 / 946, at low noise 152 / 188 / 350 and 135 / 173 /
-// 363; 2D toric L = 18, 324 checks, 16 / 256 / 1,024 shots 157 / 696 / 853 and 135 / 640 /
-// 825, 84 / 153 / 261 and 74 / 135 / 279; (6, 3) of 378 checks 265 / 1,292 / 1,377 and 224 /
-// 1,096 / 1,231. It fades towards the block's limit: L = 20, 400 checks, 16 / 256 / 1,024
-// shots 704 / 703 / 896 and 675 / 766 / 1,098, 106 / 150 / 246 and 102 / 135 / 277; with 1,024
-// threads, 3D point L = 8, it loses at every size, 16 / 256 / 1,024 shots 548 / 634 /
-// 1,236 and 601 / 710 / 1,584) -- and at any batch size on (6, 3) codes of at most 320 threads: a
-// few shots that never clear set the end of a launch of their short shots (ms
-// at one and two lanes, 32,768 shots, p = 0.03, 32 rounds and p = 0.006, 8 rounds: 36
-// checks 0.57 / 0.52 and 0.25 / 0.22, 72 2.09 / 1.60 and 0.47 / 0.44, 144 3.35 / 3.11
-// and 1.13 / 1.15; 180 checks 3.68 / 4.42 and 1.15 / 1.67, 288 7.96 / 9.94 and 2.98 /
-// 4.08, 432 9.64 / 13.8 and 3.92 / 5.92). A decode of at most two rounds, whose shots
-// all run as long, has no such end: up to 2 wavefronts per SIMD (one round, us at one and
-// two lanes: 2D toric L = 8, 64 checks, 1,024 shots 27 / 21, 4,096, 4 per SIMD, 49 / 93,
-// 8,192 82 / 139; (6, 3), 72 checks, 1,024 shots, 2 per SIMD, 46 / 36, 8,192 162 / 185; 180
-// checks, 1,024 shots, 3 per SIMD, 64 / 83; 3D point L = 5, 125 checks, 1,024 shots, 2 per
-// SIMD, 51 / 51, 4,096 144 / 177).
+// (sum-product): shorter chains per lane for the same work in all. It pays while
+// wavefronts are few -- up to 8 per SIMD counted at one lane per check, and blocks of
+// at most 900 threads (us at one and two lanes, 32 rounds at the codes' usual noise
+// and 8 at a fifth of it: 3D point L = 7, 343 checks, 16 / 256 / 1,024 shots 265 / 407
+// / 1,048 and 243 / 372 / 946, at low noise 152 / 188 / 350 and 135 / 173 / 363; 2D
+// toric L = 18, 324 checks, 16 / 256 / 1,024 shots 157 / 696 / 853 and 135 / 640 /
+// 825, 84 / 153 / 261 and 74 / 135 / 279; (6, 3) of 378 checks 265 / 1,292 / 1,377 and
+// 224 / 1,096 / 1,231. It fades towards the block's limit; (4, 2) codes of more than
+// 256 checks take it up to 2 per SIMD (L = 18, 512 shots 755 / 719, 161 / 174; L = 20,
+// 400 checks, 16 / 256 / 512 / 1,024 shots 704 / 703 / 692 / 896 and 675 / 763 / 763 /
+// 1,097, 106 / 150 / 175 / 246 and 102 / 134 / 192 / 276; 4 rounds, p = 0.05, 1,024
+// shots L = 18 318 / 339, L = 21 330 / 408); with 1,024 threads, 3D point L = 8, it
+// loses at every size, 16 / 256 / 1,024 shots 548 / 634 / 1,236 and 601 / 710 / 1,584)
+// -- and at any batch size on (6, 3) codes of at most 320 threads: a few shots that
+// never clear set the end of a launch of their short shots (ms at one and two lanes,
+// 32,768 shots, p = 0.03, 32 rounds and p = 0.006, 8 rounds: 36 checks 0.57 / 0.52 and
+// 0.25 / 0.22, 72 2.09 / 1.60 and 0.47 / 0.44, 144 3.35 / 3.11 and 1.13 / 1.15; 180
+// checks 3.68 / 4.42 and 1.15 / 1.67, 288 7.96 / 9.94 and 2.98 / 4.08, 432 9.64 / 13.8
+// and 3.92 / 5.92). A decode of at most two rounds, whose shots all run as long, has
+// no such end: up to 2 wavefronts per SIMD (one round, us at one and two lanes: 2D
+// toric L = 8, 64 checks, 1,024 shots 27 / 21, 4,096, 4 per SIMD, 49 / 93, 8,192 82 /
+// 139; (6, 3), 72 checks, 1,024 shots, 2 per SIMD, 46 / 36, 8,192 162 / 185; 180
+// checks, 1,024 shots, 3 per SIMD, 64 / 83; 3D point L = 5, 125 checks, 1,024 shots, 2
+// per SIMD, 51 / 51, 4,096 144 / 177).
 static bool pairs_pay(const DevCode& c, int bp, int dc, int dv, int reg, int64_t nshots, int cus, int spb,
                       bool brief) {
   if (bp != 1 || 2 * c.m > 900 || 2 * c.m * std::max(spb, 1) > kMaxBlock || !find_variant(dc, dv, 1, bp, reg, 0, 2))
     return false;
-  if (brief) return few_waves(nshots, c.m, 2, cus);
+  if (brief || (dc == 4 && dv == 2 && c.m > 256)) return few_waves(nshots, c.m, 2, cus);
   return (dv == 3 && 2 * c.m <= 320) || (nshots > 0 && nshots * ((c.m + 63) / 64) <= (int64_t)8 * 4 * cus);
 }
 

@@ -109,6 +109,12 @@ def test_two_lanes_per_check_on_6_3_codes(shapes, m, nshots, lanes):
     assert shape_of(shapes, m, 6, 3, 1, 1, nshots)[2] == lanes
 
 
+@pytest.mark.parametrize("m,nshots,lanes", [(256, 2048, 2), (257, 409, 2), (257, 410, 1), (324, 341, 2), (324, 342, 1),
+                                            (324, 1, 2), (441, 1024, 1), (100, 4096, 2)])
+def test_two_lanes_per_check_on_4_2_codes(shapes, m, nshots, lanes):
+    assert shape_of(shapes, m, 4, 2, 1, 1, nshots)[2] == lanes
+
+
 @pytest.mark.parametrize("dc,dv,m,nshots,cpt", [
     (6, 2, 216, 8192, 2), (6, 2, 216, 49152, 2), (6, 2, 216, 49153, 4), (6, 2, 343, 1 << 20, 2),
     (4, 4, 375, 5290, 1), (4, 4, 375, 5500, 2), (4, 4, 375, 1024, 1)])
